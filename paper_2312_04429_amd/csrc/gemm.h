@@ -50,6 +50,7 @@ struct GemmArgs {
   // filled by gemm_launch: byte extents of src1 / src2
   uint64_t bytes1, bytes2;
   int n_major;  // tile order: weight columns outermost (filled by gemm_launch)
+  int rows_ok;  // epilogue may stage rows through LDS, 8 columns a thread (filled by gemm_launch)
   int vec_ok;   // epilogue quads may use vector loads / stores (filled by gemm_launch)
 };
 

@@ -24,6 +24,7 @@
 // the float32 partials are summed in a fixed order by a second kernel that
 // applies the epilogue (deterministic).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm.h"
@@ -53,7 +54,25 @@ __device__ inline uint4 bload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-__device__ inline float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+// x Phi(x).  With a = |x| and t = 1 / (1 + 0.23 a), Phi(-a) = exp(-a^2 / 2) t P(t),
+// P a degree-7 polynomial fitted (weighted least squares over [0, 8]) to 3.9e-8
+// relative error.  Against float64 over N(0, 2^2) inputs: 2.7e-8 in the 2-norm
+// (erff: 3.5e-8, which cancels in 1 + erf for negative x), float16 results off
+// by a rounding for 0.014 % of inputs (erff: 1.5 %).  erff's two branches cost
+// a 16384 x 5120 x 640 GEGLU product about a third of its time.
+__device__ inline float gelu_erf(float x) {
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.23f, fabsf(x), 1.0f));
+  float p = -0.07659625917836188f;
+  p = fmaf(p, t, 0.2807779878031606f);
+  p = fmaf(p, t, -0.2568776671746554f);
+  p = fmaf(p, t, 0.27530439510780197f);
+  p = fmaf(p, t, -0.013266265758262716f);
+  p = fmaf(p, t, 0.11030993488071447f);
+  p = fmaf(p, t, 0.08838350014029378f);
+  p = fmaf(p, t, 0.09196435534591353f);
+  const float h = p * t * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);
+  return x * (x >= 0.0f ? 1.0f - h : h);
+}
 __device__ inline float silu(float x) { return x / (1.0f + __expf(-x)); }
 
 // Epilogue of 4 consecutive columns n..n+3 of row m (non-GEGLU): + bias,
@@ -266,6 +285,208 @@ __device__ inline void epilogue_tile(const GemmArgs& g, int64_t mb, int nb, int 
         } else {
           for (int r = 0; r < nn; ++r) o[r] = (_Float16)w[r];
         }
+      }
+    }
+  }
+}
+
+// Epilogue through LDS: the tile's float32 sums are staged row by row (IB
+// 16-row blocks of every wave row per pass), then each thread finishes 8
+// consecutive columns of one row, so that bias, row vector and residual are
+// read and the float16 result is written as 16-byte pieces of whole lines.
+// Straight from the accumulators a wave's store touches 16 rows in 32-byte
+// pieces: the last tiles of a 256 x 256 grid then take 27 us to drain.
+// GEGLU quads are combined in registers (as in epilogue_tile) and staged at
+// half the columns.  With KG > 1 wave group kg holds its share of K's sums:
+// the groups add theirs to the staged rows in group order.  The arithmetic and
+// its order are those of store_out4 / store_geglu4; the transposed columns (vt)
+// go out as 8 consecutive tokens of one channel.
+// st: LDSB bytes of LDS that no wave reads or loads into any more.  With LN,
+// ln[r] holds (mean, 1 / sqrt(var + eps)) of tile row r: the sums become
+// rstd * (sum - mean * ln_c1[n]) first.
+template <int BM, int BN, int WGM, int WGN, int KG, int LDSB, bool LN, int FM, int FN>
+__device__ __forceinline__ void epilogue_rows(const GemmArgs& g, float* st, int64_t m0, int n0, int kg,
+                                              int wm, int wn, int li, int kc,
+                                              floatx4 (&acc)[FM][FN], const float2* ln) {
+  constexpr int NT = KG * WGM * WGN * 64, WM = BM / WGM, WN = BN / WGN;
+  constexpr int SR = BN + 4;                   // staged row stride (floats)
+  constexpr int FIT = LDSB / (WGM * 16 * SR * 4);
+  constexpr int IB = FIT < FM ? FIT : FM;      // 16-row blocks per wave row and pass
+  static_assert(IB >= 1, "staging needs one 16-row block per wave row");
+  constexpr int ROWS = WGM * 16 * IB;
+  const int tid = threadIdx.x;
+  const int M = (int)min(g.M - m0, (int64_t)BM);  // rows of the tile inside the product
+  const int vt0 = g.vt ? g.vt_col0 : g.N;         // first transposed column
+  // GEGLU: quads combined in registers and staged as the finished float16
+  // outputs, BN / 2 columns a row
+  if constexpr (KG == 1 && FN % 2 == 0) {
+    if (g.geglu) {
+      constexpr int SH = BN / 2 + 8;  // staged row stride (halfs)
+      static_assert((size_t)BM * SH * 2 <= LDSB, "staged GEGLU tile");
+      _Float16* sh = (_Float16*)st;
+      float4 ba[FN / 2], bg[FN / 2];
+      floatx4 ca[FN / 2], cg[FN / 2];
+#pragma unroll
+      for (int jj = 0; jj < FN / 2; ++jj) {
+        const int na = n0 + wn * WN + 2 * jj * 16 + kc * 4;
+        const bool in = g.bias && na + 16 < g.N;
+        ba[jj] = in ? *(const float4*)(g.bias + na) : make_float4(0.f, 0.f, 0.f, 0.f);
+        bg[jj] = in ? *(const float4*)(g.bias + na + 16) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (LN) {
+          const bool cin = na + 16 < g.N;
+          ca[jj] = cin ? *(const floatx4*)(g.ln_c1 + na) : floatx4{0.f, 0.f, 0.f, 0.f};
+          cg[jj] = cin ? *(const floatx4*)(g.ln_c1 + na + 16) : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < FN / 2; ++jj) {
+          floatx4 a = acc[i][2 * jj], t = acc[i][2 * jj + 1];
+          if (LN) {
+            const float2 s = ln[wm * WM + i * 16 + li];
+            a = s.y * (a - s.x * ca[jj]);
+            t = s.y * (t - s.x * cg[jj]);
+          }
+          half4 h;
+          h[0] = (_Float16)((a[0] + ba[jj].x) * gelu_erf(t[0] + bg[jj].x));
+          h[1] = (_Float16)((a[1] + ba[jj].y) * gelu_erf(t[1] + bg[jj].y));
+          h[2] = (_Float16)((a[2] + ba[jj].z) * gelu_erf(t[2] + bg[jj].z));
+          h[3] = (_Float16)((a[3] + ba[jj].w) * gelu_erf(t[3] + bg[jj].w));
+          *(half4*)&sh[(wm * WM + i * 16 + li) * SH + wn * (WN / 2) + jj * 16 + kc * 4] = h;
+        }
+      __syncthreads();
+      constexpr int CH = BN / 16;
+      const int nout = g.N / 2 - n0 / 2;
+      for (int e = tid; e < BM * CH; e += NT) {
+        const int r = e / CH, c = (e % CH) * 8;
+        if (r < M && c < nout)
+          *(half8*)((_Float16*)g.out + (m0 + r) * g.ldo + (n0 >> 1) + c) = *(const half8*)&sh[r * SH + c];
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int i0 = 0; i0 < FM; i0 += IB) {
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      __syncthreads();
+      if (kg == k)
+#pragma unroll
+        for (int i = i0; i < i0 + IB && i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            floatx4* p = (floatx4*)&st[((wm * IB + i - i0) * 16 + li) * SR + wn * WN + j * 16 + kc * 4];
+            *p = k == 0 ? acc[i][j] : *p + acc[i][j];
+          }
+    }
+    __syncthreads();
+    auto row_of = [&](int r) { return (r / (16 * IB)) * WM + i0 * 16 + r % (16 * IB); };
+    auto live = [&](int r) { return i0 + (r % (16 * IB)) / 16 < FM && row_of(r) < M; };
+    if (g.geglu) {  // staged columns in groups of (16 "a", 16 gates); 8 outputs per thread
+      constexpr int CH = BN / 16;
+      for (int e = tid; e < ROWS * CH; e += NT) {
+        const int r = e / CH, c = e % CH;
+        const int na = (c >> 1) * 32 + (c & 1) * 8;  // first "a" column in the tile
+        if (!live(r) || n0 + na + 16 >= g.N) continue;
+        const float4* p = (const float4*)&st[r * SR + na];
+        const float4* b = (const float4*)(g.bias + n0 + na);
+        half8 h;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          float4 av = p[q], gv = p[4 + q];
+          if (LN) {
+            const float2 s = ln[row_of(r)];
+            const float4 ca = *(const float4*)(g.ln_c1 + n0 + na + 4 * q);
+            const float4 cg = *(const float4*)(g.ln_c1 + n0 + na + 16 + 4 * q);
+            av.x = s.y * (av.x - s.x * ca.x); av.y = s.y * (av.y - s.x * ca.y);
+            av.z = s.y * (av.z - s.x * ca.z); av.w = s.y * (av.w - s.x * ca.w);
+            gv.x = s.y * (gv.x - s.x * cg.x); gv.y = s.y * (gv.y - s.x * cg.y);
+            gv.z = s.y * (gv.z - s.x * cg.z); gv.w = s.y * (gv.w - s.x * cg.w);
+          }
+          if (g.bias) {
+            const float4 ba = b[q], bg = b[4 + q];
+            av.x += ba.x; av.y += ba.y; av.z += ba.z; av.w += ba.w;
+            gv.x += bg.x; gv.y += bg.y; gv.z += bg.z; gv.w += bg.w;
+          }
+          h[4 * q] = (_Float16)(av.x * gelu_erf(gv.x));
+          h[4 * q + 1] = (_Float16)(av.y * gelu_erf(gv.y));
+          h[4 * q + 2] = (_Float16)(av.z * gelu_erf(gv.z));
+          h[4 * q + 3] = (_Float16)(av.w * gelu_erf(gv.w));
+        }
+        *(half8*)((_Float16*)g.out + (m0 + row_of(r)) * g.ldo + (n0 >> 1) + c * 8) = h;
+      }
+      continue;
+    }
+    constexpr int CH = BN / 8;
+    for (int e = tid; e < ROWS * CH; e += NT) {
+      const int r = e / CH, c = e % CH;
+      const int n = n0 + c * 8;
+      if (!live(r) || n >= vt0) continue;
+      const int64_t m = m0 + row_of(r);
+      half8 res = {};
+      if (g.residual) res = *(const half8*)(g.residual + m * g.ld_res + n);
+      const float4* p = (const float4*)&st[r * SR + c * 8];
+      float4 v[2] = {p[0], p[1]};
+      if (LN) {
+        const float2 s = ln[row_of(r)];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 c1 = *(const float4*)(g.ln_c1 + n + 4 * q);
+          v[q].x = s.y * (v[q].x - s.x * c1.x); v[q].y = s.y * (v[q].y - s.x * c1.y);
+          v[q].z = s.y * (v[q].z - s.x * c1.z); v[q].w = s.y * (v[q].w - s.x * c1.w);
+        }
+      }
+      if (g.bias) {
+        const float4* b = (const float4*)(g.bias + n);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 t = b[q];
+          v[q].x += t.x; v[q].y += t.y; v[q].z += t.z; v[q].w += t.w;
+        }
+      }
+      if (g.rowvec) {
+        const float* rv = g.rowvec + (int64_t)((uint32_t)m / (uint32_t)g.rows_div) * g.ld_rowvec + n;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          v[q].x += rv[4 * q]; v[q].y += rv[4 * q + 1]; v[q].z += rv[4 * q + 2]; v[q].w += rv[4 * q + 3];
+        }
+      }
+      float w[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+      half8 h;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (g.silu) w[q] = silu(w[q]);
+        if (g.residual) w[q] += (float)res[q];
+        h[q] = (_Float16)w[q];
+      }
+      *(half8*)((_Float16*)g.out + m * g.ldo + n) = h;
+    }
+    if (n0 + BN > vt0) {  // 8 tokens of one transposed column per thread
+      constexpr int RG = ROWS / 8;
+      for (int e = tid; e < BN * RG; e += NT) {
+        const int c = e / RG, r = (e % RG) * 8;
+        const int n = n0 + c;
+        if (n < vt0 || n >= g.N || !live(r)) continue;
+        const float b = g.bias ? g.bias[n] : 0.f;
+        const float c1 = LN ? g.ln_c1[n] : 0.f;
+        half8 h;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          float v = st[(r + q) * SR + c];
+          if (LN) {
+            const float2 s = ln[row_of(r + q)];
+            v = s.y * (v - s.x * c1);
+          }
+          if (g.bias) v += b;
+          if (g.silu) v = silu(v);
+          h[q] = (_Float16)v;
+        }
+        const uint32_t m = (uint32_t)(m0 + row_of(r));
+        const uint32_t img = m / (uint32_t)g.vt_div, at = m - img * (uint32_t)g.vt_div;
+        // M, vt_div and the strides are multiples of 8
+        *(half8*)(g.vt + (int64_t)(n - vt0) * g.vt_ld + img * g.vt_stride + at) = h;
       }
     }
   }
@@ -587,9 +808,10 @@ __global__ void __launch_bounds__(256) gemm_f16(GemmArgs g, int kt_per_split) {
 // 16-byte chunk c of row r stored at chunk c ^ (r & 7): the 16 rows a quarter
 // wave reads at one k offset hit distinct bank groups.  Out-of-range rows and
 // padding taps use an offset past the descriptor's range and land as zeros.
-__device__ inline void lds_dma16(__amdgpu_buffer_rsrc_t r, uint32_t off, void* lds_wave_base) {
+__device__ inline void lds_dma16(__amdgpu_buffer_rsrc_t r, uint32_t off, void* lds_wave_base,
+                                 uint32_t soff = 0) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_wave_base,
-                                           16, off, 0, 0, 0);
+                                           16, off, soff, 0, 0);
 }
 
 // s_waitcnt with only vmcnt limited (expcnt, lgkmcnt at their maxima; gfx9 encoding).
@@ -884,6 +1106,310 @@ __global__ void __launch_bounds__(NW * 64) gemm_s(GemmArgs g, int kt_per_split) 
   epilogue_tile<FM, FN>(g, m0 + wm * WM, n0 + wn * WN, li, kc, acc);
 }
 
+// ---------------------------------------------------------------------------
+// Wide tiles and k sharing for whole-chip grids.  The kernels above multiply
+// 32 x 32 to 64 x 32 wave tiles: LDS bandwidth (fragment reads and tile writes)
+// bounds them at half the matrix rate, and a grid that leaves a CU with one
+// workgroup leaves its SIMDs one or two waves.  Here
+//   - wave tiles are up to 128 x 64 (half the fragment bytes per multiply);
+//   - where a grid of small tiles fills the chip only once, the waves of a
+//     workgroup share out k instead of the tile: KH = 2 groups take the two
+//     32-deep halves of every 64-deep tile, KT = 2 teams alternate tiles, and the
+//     groups' sums meet in the row-staged epilogue;
+//   - 64-deep k tiles (128-byte rows: whole L2 lines; 32-deep rows measured 10 %
+//     slower) move through a ring of STAGES buffers per team, and the loop is
+//     rotated: the fragments of the next half (or tile) are read while the
+//     current ones are multiplied, so a tile's buffer is free again at the
+//     barrier that follows its last fragment read.
+// LDS row layout as in gemm_s (16-byte chunk c of row r at slot c ^ (r & 7)).
+template <int FM, int FN>
+__device__ __forceinline__ void read_frags(const _Float16* __restrict__ t, int aoff, int boff,
+                                           half8 (&fa)[FM], half8 (&fb)[FN]) {
+#pragma unroll
+  for (int j = 0; j < FN; ++j) fb[j] = *(const half8*)(t + boff + j * 1024);
+#pragma unroll
+  for (int i = 0; i < FM; ++i) fa[i] = *(const half8*)(t + aoff + i * 1024);
+}
+
+template <int N>
+__device__ inline void wait_vm_lgkm0() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
+
+template <int MODE, int BM, int BN, int WGM, int WGN, int KH, int KT, int STAGES, bool LN>
+__global__ void __launch_bounds__(KT * KH * WGM * WGN * 64, 2) gemm_w(GemmArgs g) {
+  static_assert(KH == 1 || KH == 2, "halves of a k tile");
+  constexpr int NL = KH * WGM * WGN;  // waves of a team; they load its tiles
+  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
+  constexpr int GA = BM / 8, NG = GA + BN / 8;  // 8-row groups of a tile (1 KB of LDS each)
+  constexpr int PER = (NG + NL - 1) / NL;       // groups a wave loads (the last may be missing)
+  constexpr int TILE_H = (BM + BN) * 64;        // halfs per ring buffer
+  static_assert(WM % 16 == 0 && WN % 16 == 0 && STAGES >= 2, "wave tile");
+  static_assert((STAGES - 1) * PER < 64, "requests in flight per wave");
+  extern __shared__ __align__(16) unsigned char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = KT == 1 ? 0 : wave_all / NL, wave = KT == 1 ? wave_all : wave_all % NL;
+  const int kh = KH == 1 ? 0 : wave / (WGM * WGN), wt = KH == 1 ? wave : wave % (WGM * WGN);
+  const int wm = wt / WGN, wn = wt % WGN;
+  _Float16* ring = (_Float16*)smem + team * STAGES * TILE_H;
+  const int li = lane & 15, kc = lane >> 4;
+  const int ntn = (g.N + BN - 1) / BN;
+  const int mtn = (int)((g.M + BM - 1) / BM);
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t m0 = (int64_t)(g.n_major ? tile % mtn : tile / ntn) * BM;
+  const int n0 = (g.n_major ? tile / mtn : tile % ntn) * BN;
+  // this team's 64-deep k tiles: kt0, kt0 + KT, ...; every team runs
+  // the steps of team 0, its last one may find no tile left
+  const int nk = g.K / 64, kt0 = team < nk ? team : 0;  // no tile: tile 0, never multiplied
+  const int n_steps = (nk + KT - 1) / KT;
+  const int my_steps = KT == 1 ? n_steps : (nk - team + KT - 1) / KT;
+  const __amdgpu_buffer_rsrc_t rs1 = make_rsrc(g.src1, g.bytes1);
+  const __amdgpu_buffer_rsrc_t rs2 = make_rsrc(g.src2 ? g.src2 : g.src1, g.src2 ? g.bytes2 : 0);
+  const __amdgpu_buffer_rsrc_t rsw = make_rsrc(g.w, (uint32_t)((int64_t)g.N * g.ldw * 2));
+
+  // loader: group j of this wave is rows (j * NL + wave) * 8 ..+8 of the tile
+  // (A rows, then B rows); lane l loads row l / 8, slot l % 8
+  const int lrow = lane >> 3;
+  const int cch = (lane & 7) ^ lrow;
+  const bool last = NG % NL == 0 || (PER - 1) * NL + wave < NG;  // this wave has a PER-th group
+  auto is_a = [&](int j) {  // known at compile time unless group j straddles A and B rows
+    return (j + 1) * NL <= GA || (j * NL < GA && j * NL + wave < GA);
+  };
+  auto has = [&](int j) { return j + 1 < PER || last; };
+  int a_b[PER], a_oy[PER], a_ox[PER];  // conv: image, output row and column; dense: row; -1: none
+  uint32_t voff[PER];
+  const int cin = g.C1 + g.C2;
+  int t_tap = 0, t_ci = kt0 * 64;  // dense: t_ci walks [0, K)
+  if (MODE == 1) {
+    t_tap = t_ci / cin;
+    t_ci -= t_tap * cin;
+  }
+  bool t_first = true;
+  uint32_t soffA = 0, soffB = (uint32_t)kt0 * 128;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int gi = j * NL + wave;
+    a_b[j] = -1;
+    a_oy[j] = a_ox[j] = 0;
+    voff[j] = OOB;
+    if (is_a(j)) {
+      const int64_t m = m0 + gi * 8 + lrow;
+      if (m < g.M) {
+        if (MODE == 1) {
+          const int hw = g.Ho * g.Wo;
+          a_b[j] = (int)((uint32_t)m / (uint32_t)hw);
+          const int p = (int)m - a_b[j] * hw;
+          a_oy[j] = p / g.Wo;
+          a_ox[j] = p - a_oy[j] * g.Wo;
+        } else {
+          a_b[j] = (int)m;
+        }
+      }
+    } else {
+      const int n = n0 + (gi - GA) * 8 + lrow;
+      if (has(j) && n < g.N) voff[j] = (uint32_t)(((int64_t)n * g.ldw + cch * 8) * 2);
+    }
+  }
+  // offsets of the A rows at the start of the current tap and source
+  auto a_offsets = [&]() {
+    t_first = t_ci < g.C1;
+    soffA = (uint32_t)(t_first ? t_ci : t_ci - g.C1) * 2;
+    const int ky = (t_tap * 11) >> 5, kx = t_tap - 3 * ky;
+    const int ld = MODE == 1 ? (t_first ? g.C1 : g.C2) : (t_first ? g.lda1 : g.lda2);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (!is_a(j)) continue;
+      if (MODE == 0) {
+        voff[j] = a_b[j] >= 0 ? (uint32_t)(((int64_t)a_b[j] * ld + cch * 8) * 2) : OOB;
+      } else {
+        int iy, ix;
+        bool in;
+        if (g.upsample) {
+          const int uy = a_oy[j] + ky - 1, ux = a_ox[j] + kx - 1;
+          in = uy >= 0 && ux >= 0 && uy < 2 * g.Hin && ux < 2 * g.Win;
+          iy = uy >> 1;
+          ix = ux >> 1;
+        } else {
+          iy = a_oy[j] * g.stride + ky - 1;
+          ix = a_ox[j] * g.stride + kx - 1;
+          in = iy >= 0 && ix >= 0 && iy < g.Hin && ix < g.Win;
+        }
+        // below 2^31 bytes for the rows that are loaded
+        const uint32_t pix = (uint32_t)((a_b[j] * g.Hin + iy) * g.Win + ix);
+        voff[j] = a_b[j] >= 0 && in ? (pix * (uint32_t)ld + cch * 8) * 2 : OOB;
+      }
+    }
+  };
+  a_offsets();
+  int t_next = 0;  // tiles requested
+  // request the team's next tile into ring buffer `slot`; past its last tile
+  // the last one is requested again (never multiplied), so every wave's count
+  // of requests in flight stays fixed for the waits below
+  auto issue = [&](int slot) {
+    _Float16* dst = ring + slot * TILE_H;
+    // the source is uniform: branch on it, so each descriptor stays in SGPRs
+    if (__builtin_amdgcn_readfirstlane((int)t_first) != 0) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        if (is_a(j)) lds_dma16(rs1, voff[j], dst + (j * NL + wave) * 512, soffA);
+    } else {
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        if (is_a(j)) lds_dma16(rs2, voff[j], dst + (j * NL + wave) * 512, soffA);
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+      if (!is_a(j) && has(j)) lds_dma16(rsw, voff[j], dst + (j * NL + wave) * 512, soffB);
+    if (++t_next >= my_steps) return;
+    soffB += 128 * KT;
+    soffA += 128 * KT;
+    const bool was_first = t_ci < g.C1;
+    t_ci += 64 * KT;
+    bool fresh = was_first && t_ci >= g.C1;
+    if (MODE == 1)
+      while (t_ci >= cin) {
+        t_ci -= cin;
+        ++t_tap;
+        fresh = true;
+      }
+    if (fresh) a_offsets();
+  };
+  // all but the newest N tiles of this wave's requests have landed
+  auto wait_tiles = [&](auto n, bool lgkm) {
+    constexpr int N = decltype(n)::value;
+    if (NG % NL == 0 || last) {
+      if (lgkm) wait_vm_lgkm0<N * PER>();
+      else wait_vmcnt<N * PER>();
+    } else {
+      if (lgkm) wait_vm_lgkm0<N * (PER - 1)>();
+      else wait_vmcnt<N * (PER - 1)>();
+    }
+  };
+
+  // Folded LayerNorm: TPR threads of the team per A row each sum CPT of its
+  // eight 16-byte chunks per tile, shifted by the row's first value so that the
+  // one-pass variance does not cancel (float16 shift, float32 dot2); the teams'
+  // sums meet in LDS after the loop.
+  constexpr int TPR = NL * 64 / BM, CPT = TPR > 0 ? 8 / TPR : 1;
+  static_assert(!LN || (TPR >= 1 && TPR <= 8 && 8 % TPR == 0), "LayerNorm rows per team");
+  const int ttid = tid % (NL * 64), st_row = LN ? ttid / TPR : 0, st_slot = LN ? (ttid % TPR) * CPT : 0;
+  half2v st_shift = {(_Float16)0.f, (_Float16)0.f};
+  float st_s1 = 0.f, st_s2 = 0.f;
+  if (LN && m0 + st_row < g.M) {
+    const _Float16 x0 = g.src1[(m0 + st_row) * g.lda1];
+    st_shift = half2v{x0, x0};
+  }
+  auto stats = [&](int sl) {
+    if constexpr (LN) {
+      const _Float16* ar = ring + sl * TILE_H + st_row * 64;
+      const half2v one = {(_Float16)1.f, (_Float16)1.f};
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        const half8 x = *(const half8*)(ar + (st_slot + c) * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const half2v d = half2v{x[2 * e], x[2 * e + 1]} - st_shift;
+          st_s1 = __builtin_amdgcn_fdot2(d, one, st_s1, false);
+          st_s2 = __builtin_amdgcn_fdot2(d, d, st_s2, false);
+        }
+      }
+    }
+  };
+
+  floatx4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int arow = (wm * WM + li) * 64, brow = (BM + wn * WN + li) * 64;
+  const int s0 = ((kh * 4 + kc) ^ (li & 7)) << 3;  // slot of this group's (first) half
+  const int s1 = ((4 + kc) ^ (li & 7)) << 3;       // second half (KH == 1)
+  half8 fa0[FM], fb0[FN], fa1[FM], fb1[FN];
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s) issue(s);
+  wait_tiles(std::integral_constant<int, STAGES - 1>{}, false);
+  ring_barrier();
+  read_frags<FM, FN>(ring, arow + s0, brow + s0, fa0, fb0);
+  int slot = 0;  // ring buffer of the tile being multiplied
+  if (LN && my_steps > 0) stats(0);
+  // multiply the current fragments while the next ones are read (the reads go
+  // out between the first multiplies)
+  auto mma = [&](half8 (&ca)[FM], half8 (&cb)[FN]) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cb[j], ca[i], acc[i][j], 0, 0, 0);
+    constexpr int PER_READ = (FM * FN * 3 / 4) / (FM + FN) > 0 ? (FM * FN * 3 / 4) / (FM + FN) : 1;
+#pragma unroll
+    for (int r = 0; r < FM + FN; ++r) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);         // one LDS read
+      __builtin_amdgcn_sched_group_barrier(0x008, PER_READ, 0);  // multiplies
+    }
+  };
+  // this wave's reads of the current tile are done and its part of the next
+  // one has landed; after the barrier that holds for every wave
+  auto turn = [&]() {
+    wait_tiles(std::integral_constant<int, STAGES - 2>{}, true);
+    ring_barrier();
+    issue(slot);
+    slot = slot + 1 == STAGES ? 0 : slot + 1;
+  };
+  if constexpr (KH == 1) {
+    for (int t = 0; t < n_steps; ++t) {
+      read_frags<FM, FN>(ring + slot * TILE_H, arow + s1, brow + s1, fa1, fb1);
+      if (KT == 1 || t < my_steps) mma(fa0, fb0);
+      turn();
+      read_frags<FM, FN>(ring + slot * TILE_H, arow + s0, brow + s0, fa0, fb0);
+      if (KT == 1 || t < my_steps) mma(fa1, fb1);
+      if (LN && t + 1 < my_steps) stats(slot);
+    }
+  } else {
+    auto step = [&](int t, half8 (&ca)[FM], half8 (&cb)[FN], half8 (&na)[FM], half8 (&nb)[FN]) {
+      turn();
+      read_frags<FM, FN>(ring + slot * TILE_H, arow + s0, brow + s0, na, nb);
+      if (KT == 1 || t < my_steps) mma(ca, cb);
+      if (LN && t + 1 < my_steps) stats(slot);
+    };
+    int t = 0;
+    for (; t + 1 < n_steps; t += 2) {
+      step(t, fa0, fb0, fa1, fb1);
+      step(t + 1, fa1, fb1, fa0, fb0);
+    }
+    if (t < n_steps) step(t, fa0, fb0, fa1, fb1);
+  }
+  wait_vmcnt<0>();  // drain the requests past the last tile before LDS is reused
+
+  __shared__ float2 lnst[LN ? KT * BM : 1];
+  if constexpr (LN) {
+#pragma unroll
+    for (int o = 1; o < TPR; o <<= 1) {
+      st_s1 += __shfl_xor(st_s1, o, 64);
+      st_s2 += __shfl_xor(st_s2, o, 64);
+    }
+    if (ttid % TPR == 0) lnst[team * BM + st_row] = make_float2(st_s1, st_s2);
+    __syncthreads();
+    if (team == 0 && ttid % TPR == 0) {
+      float2 u = lnst[st_row];
+#pragma unroll
+      for (int k = 1; k < KT; ++k) {
+        u.x += lnst[k * BM + st_row].x;
+        u.y += lnst[k * BM + st_row].y;
+      }
+      const float inv_k = 1.0f / (float)g.K;
+      const float mu = u.x * inv_k;
+      const float var = fmaxf(u.y * inv_k - mu * mu, 0.f);
+      lnst[st_row] = make_float2((float)st_shift[0] + mu, rsqrtf(var + g.ln_eps));
+    }  // published by the epilogue's first barrier
+    if (g.geglu) __syncthreads();  // whose GEGLU form reads the rows before it
+  }
+  epilogue_rows<BM, BN, WGM, WGN, KH * KT, KT * STAGES * TILE_H * 2, LN>(
+      g, (float*)smem, m0, n0, team * KH + kh, wm, wn, li, kc, acc, lnst);
+}
+
 // Sum split-K partials in split order and apply the epilogue, four
 // consecutive columns per thread (N % 4 == 0, checked by the launcher).  The
 // loads of up to RED_CHUNK splits are issued together before their adds (a
@@ -1097,6 +1623,42 @@ hipError_t launch_s(const GemmArgs& g, int splits, hipStream_t s) {
   return launch_s_t<MODE, BM, BN, STAGES, false, U, NW>(g, splits, s);
 }
 
+template <int MODE, int BM, int BN, int WGM, int WGN, int KH, int KT, int STAGES, bool LN>
+hipError_t launch_w_t(const GemmArgs& g, hipStream_t s) {
+  constexpr int NW = KT * KH * WGM * WGN;
+  // GEGLU's 32-column groups may not straddle tiles
+  if (!g.rows_ok || g.K % 64 != 0 || (g.geglu && BN % 32 != 0)) return hipErrorInvalidValue;
+  if (g.bytes1 >= 0x80000000u || g.bytes2 >= 0x80000000u ||
+      (int64_t)g.N * g.ldw * 2 >= 0x80000000ll)
+    return hipErrorInvalidValue;  // descriptors address less than 2 GiB (gemm_launch chunks)
+  constexpr size_t lds = (size_t)KT * STAGES * (BM + BN) * 64 * 2;
+  static_assert(lds <= 160 * 1024, "LDS per workgroup");
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_w<MODE, BM, BN, WGM, WGN, KH, KT, STAGES, LN>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  dim3 grid((unsigned)(ceil_div(g.M, BM) * ceil_div(g.N, BN)));
+  const int fam = MODE == 1 ? NV_FAM_CONV : NV_FAM_LINEAR;
+  const double flops = 2.0 * (double)g.M * g.N * g.K;
+  const double bytes = (double)g.bytes1 + g.bytes2 + (double)g.N * g.K * 2 +
+                       (double)g.M * (g.geglu ? g.N / 2 : g.N) * 2;
+  const TraceEv ev =
+      trace_begin(fam, flops, bytes, TraceShape{g.M, g.N, g.K, BM * 10000 + BN * 10 + 1});
+  hipExtLaunchKernelGGL((gemm_w<MODE, BM, BN, WGM, WGN, KH, KT, STAGES, LN>), grid, dim3(NW * 64),
+                        (uint32_t)lds, s, ev.a, ev.b, 0u, g);
+  return hipGetLastError();
+}
+
+template <int MODE, int BM, int BN, int WGM, int WGN, int KH, int KT, int STAGES>
+hipError_t launch_w(const GemmArgs& g, hipStream_t s) {
+  if constexpr (MODE == 0)
+    if (g.ln_c1) return launch_w_t<0, BM, BN, WGM, WGN, KH, KT, STAGES, true>(g, s);
+  return launch_w_t<MODE, BM, BN, WGM, WGN, KH, KT, STAGES, false>(g, s);
+}
+
 // Streamed kernel when every 64-deep k tile lies inside one source and tap.
 template <int MODE>
 bool streamable(const GemmArgs& g) {
@@ -1114,6 +1676,82 @@ hipError_t launch(const GemmArgs& g, int splits, hipStream_t s) {
               : launch_t<MODE, BM, BN, false>(g, splits, s);
 }
 
+// Forms of the wide kernel with their measured cost in us: a launch costs
+// about 5, a round of tiles f + s per 64-deep k tile (f1, s1 with one
+// workgroup per CU; f2, s2 with two where two fit, both finishing).  The
+// constants are linear fits to graph-free timings on the UNet's shapes (6 to
+// 180 k tiles, 80 to 2560 tiles), which they match within about 8 %:
+// 4096 x 1280 x 5120 56 us (128 x 128 tiles of gemm_s: 77), 4096 x 3840 x 1280
+// 45 (54), 65536 x 960 x 320 73 (82), 2048 x 640 x 2560 16.2 (22.5), 1024 x
+// 1280 x 5120 26 (35), 3x3 convolutions over 16 x 32 x 32 640 -> 640 105
+// (145), 16 x 16 x 16 1280 -> 1280 117 (150), 2 x 32 x 32 640 -> 640 28 (34.5).
+struct WideForm {
+  int bm, bn, per_cu;
+  float f1, s1, f2, s2;
+};
+constexpr WideForm WIDE[] = {
+    {256, 256, 1, 10.0f, 1.40f, 0.f, 0.f},   // 0: 8 waves of 128 x 64
+    {256, 160, 1, 8.5f, 1.02f, 0.f, 0.f},    // 1: 8 waves of 64 x 80
+    {128, 160, 2, 5.0f, 0.65f, 7.0f, 1.12f}, // 2: 8 waves of 32 x 80
+    {128, 160, 1, 6.0f, 0.58f, 0.f, 0.f},    // 3: 2 k halves x 4 waves of 64 x 80
+    {128, 128, 2, 1.4f, 0.59f, 5.2f, 0.94f}, // 4: 8 waves of 64 x 32
+    {64, 160, 1, 2.0f, 0.385f, 0.f, 0.f},    // 5: 2 k halves x 4 waves of 32 x 80
+    {128, 80, 2, 1.7f, 0.37f, 4.0f, 0.68f},  // 6: 2 k halves x 4 waves of 32 x 80
+    {64, 128, 2, 0.3f, 0.29f, 4.2f, 0.58f},  // 7: 2 k halves x 4 waves of 32 x 64
+    {64, 80, 1, 1.0f, 0.25f, 0.f, 0.f},      // 8: 2 k halves x 2 teams x 2 waves of 32 x 80
+    {64, 64, 2, 0.2f, 0.19f, 1.6f, 0.375f},  // 9: 2 k halves x 4 waves of 32 x 32
+};
+constexpr int NCU = 256;
+
+float wide_cost(const WideForm& w, const GemmArgs& g) {
+  const int64_t tiles = ceil_div(g.M, w.bm) * ceil_div(g.N, w.bn);
+  const float n = (float)(g.K / 64), one = w.f1 + n * w.s1;
+  if (w.per_cu == 1) return 5.0f + (float)ceil_div(tiles, NCU) * one;
+  const int64_t rem = tiles % (2 * NCU);
+  const float two = w.f2 + n * w.s2;
+  return 5.0f + (float)(tiles / (2 * NCU)) * two + (rem == 0 ? 0.f : rem <= NCU ? one : two);
+}
+
+// The cheapest form, or -1 where the kernels below are the better choice: the
+// row-staged epilogue does not apply, or K is long enough over a grid small
+// enough that split K pays (about 10 us + 650 TFLOP/s with its reduction:
+// 2 x 16 x 16 1280 -> 1280 32.5 us against 39 to 46).  GEGLU combines its quads
+// in registers (forms 0 and 4) or, on small grids, from the staged rows.
+int wide_form(const GemmArgs& g) {
+  if (!g.rows_ok) return -1;
+  int best = -1;
+  float cost = 1e30f;
+  for (int i = 0; i < (int)(sizeof(WIDE) / sizeof(WIDE[0])); ++i) {
+    if (g.geglu && i != 0 && i != 4 && i != 7) continue;
+    const float c = wide_cost(WIDE[i], g);
+    if (c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  const bool can_split = g.partial && !g.ln_c1 && !g.geglu && g.K / 64 >= 20 &&
+                         (size_t)2 * g.M * g.N * 4 <= g.partial_bytes;
+  if (can_split && 10.0f + 2.0f * (float)g.M * (float)g.N * (float)g.K / 650e6f < cost) return -1;
+  return best;
+}
+
+template <int MODE>
+hipError_t dispatch_wide(const GemmArgs& g, int form, hipStream_t s) {
+  switch (form) {
+    case 0: return launch_w<MODE, 256, 256, 2, 4, 1, 1, 2>(g, s);
+    case 1: return launch_w<MODE, 256, 160, 4, 2, 1, 1, 2>(g, s);
+    case 2: return launch_w<MODE, 128, 160, 4, 2, 1, 1, 2>(g, s);
+    case 3: return launch_w<MODE, 128, 160, 2, 2, 2, 1, 3>(g, s);
+    case 4: return launch_w<MODE, 128, 128, 2, 4, 1, 1, 2>(g, s);
+    case 5: return launch_w<MODE, 64, 160, 2, 2, 2, 1, 4>(g, s);
+    case 6: return launch_w<MODE, 128, 80, 4, 1, 2, 1, 3>(g, s);
+    case 7: return launch_w<MODE, 64, 128, 2, 2, 2, 1, 3>(g, s);
+    case 8: return launch_w<MODE, 64, 80, 2, 1, 2, 2, 3>(g, s);
+    case 9: return launch_w<MODE, 64, 64, 2, 2, 2, 1, 4>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // Tile choice for the streamed kernel (GPU time measured on the UNet's
 // shapes).  A workgroup here is bound by the latency of its k-tile loads
 // (about 0.4 us per tile), so small tiles and many resident workgroups win:
@@ -1126,6 +1764,8 @@ hipError_t launch(const GemmArgs& g, int splits, hipStream_t s) {
 // deep convolution over 32 to 128 such tiles, take split 128 x 128.
 template <int MODE>
 hipError_t dispatch_streamed(const GemmArgs& g, hipStream_t s) {
+  const int form = wide_form(g);
+  if (form >= 0) return dispatch_wide<MODE>(g, form, s);
   constexpr int MIN_KT = 10;
   const int nk = g.K / 64;
   const int64_t t128 = ceil_div(g.M, 128) * ceil_div(g.N, 128);
@@ -1240,6 +1880,14 @@ hipError_t gemm_launch_one(const GemmArgs& gin, hipStream_t s) {
   g.vec_ok = (g.N % 4 == 0) && (g.ldo % 4 == 0) && al(g.out, g.out_f32 ? 16 : 8) &&
              (!g.bias || al(g.bias, 16)) &&
              (!g.residual || ((g.ld_res % 4 == 0) && al(g.residual, 8)));
+  // the row-staged epilogue: 8 float16 columns (or 8 tokens of a transposed
+  // column) per thread as one 16-byte access
+  g.rows_ok = g.vec_ok && !g.out_f32 && g.M < (int64_t(1) << 31) && g.N % (g.geglu ? 32 : 8) == 0 &&
+              g.ldo % 8 == 0 && al(g.out, 16) && (!g.rowvec || g.rows_div < (int64_t(1) << 31)) &&
+              (!g.residual || (g.ld_res % 8 == 0 && al(g.residual, 16))) &&
+              (!g.vt || (!g.geglu && g.M % 8 == 0 && g.vt_col0 % 8 == 0 && g.vt_ld % 8 == 0 &&
+                         g.vt_div % 8 == 0 && g.vt_div < (int64_t(1) << 31) &&
+                         g.vt_stride % 8 == 0 && al(g.vt, 16)));
   return g.conv ? dispatch<1>(g, s) : dispatch<0>(g, s);
 }
 
