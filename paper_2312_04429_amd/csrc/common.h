@@ -75,6 +75,16 @@ __device__ inline float rows_max(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// The same lanes' sum.
+__device__ inline float rows_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                  false);
+  const float m = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false,
+                                                  false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // Sum over the 64 lanes of a wave, the total in every lane, without LDS: DPP
 // adds within each 16-lane row (lane ^ 1, lane ^ 2 by quad permutes, then the
 // row rotated by 4 and by 8), then the row swaps across rows.

@@ -81,29 +81,6 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 }
 __device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-template <typename T>
-__device__ inline T block_max_256(T v, T* red) {
-  for (int o = 32; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    v = v > w ? v : w;
-  }
-  const int wid = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[wid] = v;
-  __syncthreads();
-  T r = red[0];
-  for (int i = 1; i < 4; ++i) r = r > red[i] ? r : red[i];
-  return r;
-}
-
-__device__ inline double block_sum_256(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
-}
-
 // Per query: bf16 copy (padded rows are zero) and the margin factor E_q.
 __global__ void __launch_bounds__(256) lk_prep(const float* __restrict__ q, int m, int mq_pad,
                                                int d, int dp, int cache_bf16,
@@ -190,6 +167,10 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
 
+// Caller arrays are only known to be element aligned; the hardware takes
+// 16-byte loads at 4-byte addresses.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
@@ -206,6 +187,27 @@ __device__ inline void dma_queries(uint16_t* sQ, const LookupWs& ws, int q0) {
     if (base + lane < nc)
       __builtin_amdgcn_global_load_lds((gptr_t)(src + (size_t)(base + lane) * 16),
                                        (lptr_t)((char*)sQ + (size_t)base * 16), 16, 0, 0);
+}
+
+// The first query block straight from the float32 queries (calls of one or
+// two queries): rounded, zero padded and swizzled as lk_prep stores it.
+__device__ inline void convert_queries(uint16_t* sQ, const float* __restrict__ queries, int m, int d,
+                                       int dp) {
+  const int nc = dp / 8;
+  for (int i = threadIdx.x; i < QB * nc; i += 256) {
+    const int r = i / nc, c = i - r * nc;
+    float4u v[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    if (r < m && c * 8 < d) {
+      v[0] = *(const float4u*)(queries + (int64_t)r * d + c * 8);
+      v[1] = *(const float4u*)(queries + (int64_t)r * d + c * 8 + 4);
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      w[e] = (uint32_t)f32_to_bf16_rne(v[e >> 1][2 * (e & 1)]) |
+             ((uint32_t)f32_to_bf16_rne(v[e >> 1][2 * (e & 1) + 1]) << 16);
+    *(uint4*)(sQ + qpos(r, c * 8, dp)) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
 }
 
 // Stage one 16-query block of bf16 queries into LDS.
@@ -364,7 +366,8 @@ __device__ inline void bare_barrier() {
 // workgroups share a CU, so one loads while the other multiplies.
 template <int NS>
 __global__ void __launch_bounds__(256, 2) lk_scan_bf16(const uint16_t* __restrict__ cache,
-                                                          int64_t n, int d, int m, LookupWs ws) {
+                                                          int64_t n, int d, int m, LookupWs ws,
+                                                          const float* __restrict__ queries) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int dp = NS * 32;      // == ws.dp
   constexpr int DMA = NS / 4;      // global -> LDS requests per wave per query block
@@ -399,7 +402,10 @@ __global__ void __launch_bounds__(256, 2) lk_scan_bf16(const uint16_t* __restric
   const int nb = (m + QB - 1) / QB;
   const int b0 = (tile >> 3) % nb;  // tiles t, t + 8, ... share an XCD
   auto blk = [&](int i) { const int b = b0 + i; return (b >= nb ? b - nb : b) * QB; };
-  dma_queries(sQ, ws, blk(0));
+  if (queries)  // one block, not converted by lk_prep
+    convert_queries(sQ, queries, m, d, dp);
+  else
+    dma_queries(sQ, ws, blk(0));
   if (nb > 1) dma_queries(sQ + QB * dp, ws, blk(1));
   if (nb > 2) dma_queries(sQ + 2 * QB * dp, ws, blk(2));
 #pragma unroll
@@ -453,47 +459,295 @@ __global__ void __launch_bounds__(256, 2) lk_scan_bf16(const uint16_t* __restric
   __builtin_amdgcn_s_waitcnt(0);
 }
 
-// f32 cache: one thread per row, 16 queries at a time, d in chunks of 256.
-__global__ void __launch_bounds__(256) lk_scan_f32(const float* __restrict__ cache, int64_t n,
-                                                   int d, const float* __restrict__ queries, int m,
-                                                   LookupWs ws) {
-  __shared__ float sQ[QB * 256];
-  __shared__ float sS[2][QB * SS_WIDE];
-  __shared__ float sN[TILE];
-  const int tile = blockIdx.x;
-  const int r = threadIdx.x;
-  const int64_t row = (int64_t)tile * TILE + r;
-  const int rows = (int)min((int64_t)TILE, n - (int64_t)tile * TILE);
-  const bool rv = row < n;
-  const float* crow = cache + (rv ? row : 0) * (int64_t)d;
-  for (int q0 = 0; q0 < m; q0 += QB) {
-    const int qcount = min(QB, m - q0);
-    float acc[QB];
+// bf16 cache with d <= 768 and many queries: the roles turned round.  Each of
+// 4 waves holds NBW blocks of 16 queries (the whole k range, NBW * NS * 4
+// registers; 256 queries at NBW = 4) and the cache rows stream once through a
+// ring of R 16-row blocks in LDS (global -> LDS loads, no registers), so a
+// persistent workgroup per CU keeps HBM busy while it multiplies and an LDS
+// read of 1 KB feeds NBW multiplies instead of two (LDS reads bound the
+// kernel above at many queries: 256 queries over 4 M rows 2239 us against 1675,
+// 128 queries 1550 against 1238; at 64 the two are equal).  One wave per SIMD: the first PF fragments of the next block are
+// read ahead across the barrier.  Chunk c of row r sits at chunk c ^ (r & 15)
+// of its LDS row, as the queries do above.
+constexpr int MANY_M = 64;  // queries beyond which lk_scan_many is used
+constexpr int MANY_R = 6;  // row blocks in the ring (147 KB at d = 768)
+
+template <int NS, int NBW>
+__global__ void __launch_bounds__(256, 1) lk_scan_many(const uint16_t* __restrict__ cache,
+                                                       int64_t n, int d, int m, LookupWs ws) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int R = MANY_R;
+  constexpr int dp = NS * 32, BLK = 16 * dp;  // halfs per row block
+  constexpr int DMA = NS / 4;                 // requests per wave per row block
+  constexpr int PF = 4;
+  uint16_t* ring = (uint16_t*)smem;           // [R][16][dp]
+  float* sN = (float*)(ring + (size_t)R * BLK);  // [2][4 waves] largest squared row norm of a tile
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, kc = lane >> 4;
+  const int q0 = blockIdx.y * 64 * NBW + wave * 16 * NBW;  // first query of this wave
+  const int64_t nblk = (n + 15) / 16;
+  // tiles of 8 row blocks, dealt round-robin to the workgroups
+  const int T = ws.T, G = gridDim.x;
+  const int my_tiles = ((int)blockIdx.x < T) ? (T - 1 - (int)blockIdx.x) / G + 1 : 0;
+  const int nb = my_tiles * 8;
+  // query fragments: query q0 + b * 16 + li, k = j * 32 + kc * 8
+  u32x4 qf[NBW][NS];
 #pragma unroll
-    for (int q = 0; q < QB; ++q) acc[q] = 0.f;
-    float nn = 0.f;
-    for (int k0 = 0; k0 < d; k0 += 256) {
-      const int kn = min(256, d - k0);
-      __syncthreads();
-      for (int i = threadIdx.x; i < QB * 256; i += 256) {
-        const int q = i / 256, k = i % 256;
-        sQ[i] = (q < qcount && k < kn) ? queries[(int64_t)(q0 + q) * d + k0 + k] : 0.f;
+  for (int b = 0; b < NBW; ++b)
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int q = q0 + b * 16 + li;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (q < ws.mq) v = *(const u32x4*)(ws.qbf + (int64_t)q * dp + ((((j * 4 + kc) ^ (q & 15))) << 3));
+      qf[b][j] = v;
+    }
+  // row block i of this workgroup (tile i / 8 of its list): its rows and a
+  // descriptor over them; requests past the last block read nothing
+  auto rows_of = [&](int i, int64_t* row) {
+    *row = ((int64_t)blockIdx.x + (int64_t)(i >> 3) * G) * RR_TILE + (i & 7) * 16;
+    const int64_t left = n - *row;
+    return i < nb && left > 0 ? (int)min((int64_t)16, left) : 0;
+  };
+  // request part u of a block into its slot
+  auto dma = [&](int u, int64_t row, int rows, int slot) {
+    const int p = (u * 4 + wave) * 64 + lane;         // chunk position in the block
+    const int r = p / (dp / 8), sl = p % (dp / 8);
+    const int c = (sl & ~15) | ((sl ^ r) & 15);
+    const uint32_t off = c * 8 < d ? (uint32_t)((r * d + c * 8) * 2) : OOB;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(cache + (rows > 0 ? row * d : 0), (uint32_t)rows * d * 2);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        rs, (lptr_t)((char*)(ring + (size_t)slot * BLK) + (u * 4 + wave) * 1024), 16, off, 0, 0, 0);
+  };
+  for (int i = 0; i < R - 1; ++i) {
+    int64_t row;
+    const int rows = rows_of(i, &row);
+#pragma unroll
+    for (int u = 0; u < DMA; ++u) dma(u, row, rows, i);
+  }
+  // fragment j of a row block: row li, chunk j * 4 + kc at slot (j * 4 + kc) ^ li
+  const int x2 = li >> 2;
+  const int base = li * dp + 8 * (kc ^ (li & 3));
+  const int off4[4] = {base + 32 * (0 ^ x2), base + 32 * ((1 ^ x2) - 1), base + 32 * ((2 ^ x2) - 2),
+                       base + 32 * ((3 ^ x2) - 3)};
+  auto frag = [&](const uint16_t* __restrict__ blkp, int j) {
+    return *(const u32x4*)(blkp + off4[j & 3] + 32 * j);
+  };
+  floatx4 acc[NBW];
+  float tmax[NBW];
+  float nmax = 0.f;
+  u32x4 pf[PF];
+  int slot = 0;
+  // blocks 0 and 1 have landed (of the R - 1 requested)
+  wait_vm_lgkm0<(R - 3) * DMA>();
+  bare_barrier();
+#pragma unroll
+  for (int j = 0; j < PF; ++j) pf[j] = frag(ring, j);
+  for (int i = 0; i < nb; ++i) {
+    const uint16_t* cur = ring + (size_t)slot * BLK;
+    const int nslot = slot + 1 == R ? 0 : slot + 1;
+    const uint16_t* nxt = ring + (size_t)nslot * BLK;
+    if ((i & 7) == 0) {
+#pragma unroll
+      for (int b = 0; b < NBW; ++b) tmax[b] = -INFINITY;
+      nmax = 0.f;
+    }
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // Fragments roll through PF registers, PF steps ahead of their multiplies
+    // and on into the next block.  Block i + R - 1 goes to the slot that the
+    // last barrier freed, one request every four steps, so that its issue hides
+    // under the multiplies.  Each wave sums the row norms of every fourth block
+    // (of every block: 455 us per million rows at 256 queries; none: 348).
+    int64_t drow;
+    const int drows = rows_of(i + R - 1, &drow);
+    const int dslot = slot == 0 ? R - 1 : slot - 1;
+    const bool own = (i & 3) == wave;  // uniform
+    {
+      float nn0 = 0.f, nn1 = 0.f;
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        if (j % 4 == 1) dma(j / 4, drow, drows, dslot);
+        const u32x4 w = pf[j % PF];
+        const u32x4 next = j + PF < NS ? frag(cur, j + PF) : frag(nxt, j + PF - NS);
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)&w,
+                                                           *(const bf16x8*)&qf[b][j], acc[b], 0, 0, 0);
+        if (own)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t we = w[e];  // via a scalar (see the wide scan)
+            const bf16x2 v = __builtin_bit_cast(bf16x2, we);
+            float& nn = (e & 1) ? nn1 : nn0;
+            nn = __builtin_amdgcn_fdot2_f32_bf16(v, v, nn, false);
+          }
+        pf[j % PF] = next;
+        __builtin_amdgcn_sched_barrier(0);  // keeps the reads PF steps ahead
       }
-      __syncthreads();
-      for (int k = 0; k < kn; ++k) {
-        const float c = rv ? crow[k0 + k] : 0.f;
-        nn = fmaf(c, c, nn);
+      // sum over the row's four lanes (row swaps, no LDS); rows past n are zero
+      if (own) nmax = fmaxf(nmax, rows_sum(nn0 + nn1));
+    }
+    const int tile = (int)blockIdx.x + (i >> 3) * G;
+    const int64_t row = (int64_t)tile * RR_TILE + (i & 7) * 16;
+    if (row + 16 <= n) {
 #pragma unroll
-        for (int q = 0; q < QB; ++q) acc[q] = fmaf(sQ[q * 256 + k], c, acc[q]);
+      for (int b = 0; b < NBW; ++b) {
+        // max without the NaN quieting of fmaxf (a NaN score loses either way)
+        tmax[b] = __builtin_amdgcn_fmed3f(tmax[b], acc[b][0], INFINITY);
+        tmax[b] = __builtin_amdgcn_fmed3f(tmax[b], acc[b][1], INFINITY);
+        tmax[b] = __builtin_amdgcn_fmed3f(tmax[b], acc[b][2], INFINITY);
+        tmax[b] = __builtin_amdgcn_fmed3f(tmax[b], acc[b][3], INFINITY);
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (row + kc * 4 + r < n) tmax[b] = fmaxf(tmax[b], acc[b][r]);
+    }
+    if ((i & 7) == 7) {  // tile complete
+#pragma unroll
+      for (int b = 0; b < NBW; ++b) {
+        const float v = rows_max(tmax[b]);
+        const int q = q0 + b * 16 + li;
+        if (kc == 0 && q < ws.mq) ws.tmax[tmax_at(ws, q, tile)] = v;
+      }
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) nmax = fmaxf(nmax, __shfl_xor(nmax, o, 64));
+      if (lane == 0) sN[((i >> 3) & 1) * 4 + wave] = nmax;
+    }
+    // this wave has read the block and its parts of blocks i + 1 and i + 2
+    // have landed (i + 2's first fragments are read before the next barrier);
+    // stores of tmax are in the count too, which only waits for more
+    wait_vm_lgkm0<(R - 3) * DMA>();
+    bare_barrier();
+    if ((i & 7) == 7 && tid == 0 && blockIdx.y == 0) {
+      const float* N = sN + ((i >> 3) & 1) * 4;
+      ws.nmax[tile] = sqrtf(fmaxf(fmaxf(N[0], N[1]), fmaxf(N[2], N[3])) * 1.001f);
+    }
+    slot = nslot;
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
+// f32 cache: 8 waves of 32 rows (two 16-row blocks) per 256-row tile, fp32
+// matrix cores (16x16x4), QN blocks of 16 queries in LDS per pass over the
+// rows.  Lane (li, kc) loads four consecutive k (16 bytes, 4 kc past each
+// group of 16) of row li, and step e of a group multiplies every lane's e-th
+// value: some order of the same products, which is all the scan bound needs.
+// Two 64-deep chunks per row block are in flight; HBM bounds the kernel (one
+// thread per row, as before, reads 4 bytes of 64 rows at a time: 300 k x 768,
+// 4 queries 1218 us against 180 us, 5.1 TB/s).  Query rows are 16 bytes longer than a
+// multiple of 64 bytes, so that the 16 rows of a read fall into distinct bank
+// groups.
+constexpr int F32_T = 512;
+__host__ __device__ inline int f32_qrow(int d) { return (d + 63) / 64 * 64 + 4; }  // floats
+
+template <int QN>
+__global__ void __launch_bounds__(F32_T) lk_scan_f32(const float* __restrict__ cache, int64_t n,
+                                                     int d, const float* __restrict__ queries,
+                                                     int m, LookupWs ws) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int qr = f32_qrow(d);
+  float* sQ = (float*)smem;                      // [QN * QB][qr]
+  float* sM = sQ + (size_t)QN * QB * qr;         // [8 waves][QN * QB]
+  float* sN = sM + 8 * QN * QB;                  // [TILE]
+  const int tile = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, kc = lane >> 4;
+  const int64_t row0 = (int64_t)tile * TILE;
+  const int rows = (int)min((int64_t)TILE, n - row0);
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(cache + row0 * d, (uint32_t)rows * d * 4);
+  const int nc = (d + 63) / 64;  // 64-deep chunks
+  auto fetch = [&](int c, u32x4(&a)[2][4]) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int rloc = wave * 32 + b * 16 + li;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = c * 64 + u * 16 + kc * 4;
+        const uint32_t off = rloc < rows && k < d ? (uint32_t)((rloc * d + k) * 4) : OOB;
+        a[b][u] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
       }
     }
-    float* S = sS[(q0 / QB) & 1];
-#pragma unroll
-    for (int q = 0; q < QB; ++q) S[q * SS_WIDE + r] = acc[q];
-    if (q0 == 0) sN[r] = sqrtf(nn * 1.001f);
+  };
+  for (int q0 = 0; q0 < m; q0 += QN * QB) {
+    const bool norms = q0 == 0;  // row norms during the first pass
+    u32x4 a0[2][4], a1[2][4];
+    fetch(0, a0);
+    if (nc > 1) fetch(1, a1);
+    __syncthreads();  // every wave is past the previous pass
+    for (int i = tid; i < QN * QB * (qr / 4); i += F32_T) {
+      const int q = i / (qr / 4), k = (i % (qr / 4)) * 4;
+      float4u v = {0.f, 0.f, 0.f, 0.f};
+      if (q0 + q < m && k < d) v = *(const float4u*)(queries + (int64_t)(q0 + q) * d + k);
+      *(floatx4*)&sQ[q * qr + k] = v;
+    }
     __syncthreads();
-    if (q0 == 0) write_norm_max<TILE>(sN, rows, tile, ws);
-    write_tile_max<TILE, SS_WIDE>(S, rows, tile, q0, ws);
+    floatx4 acc[2][QN];
+    float nn[2] = {0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int j = 0; j < QN; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto consume = [&](int c, const u32x4(&a)[2][4]) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float4 qv[QN];
+#pragma unroll
+        for (int j = 0; j < QN; ++j)
+          qv[j] = *(const float4*)&sQ[(j * QB + li) * qr + c * 64 + u * 16 + kc * 4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const float x = __uint_as_float(a[b][u][e]);
+            nn[b] = fmaf(x, x, nn[b]);
+#pragma unroll
+            for (int j = 0; j < QN; ++j)
+              acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, ((const float*)&qv[j])[e],
+                                                               acc[b][j], 0, 0, 0);
+          }
+      }
+    };
+    for (int c = 0; c < nc; c += 2) {
+      consume(c, a0);
+      if (c + 2 < nc) fetch(c + 2, a0);
+      if (c + 1 < nc) {
+        consume(c + 1, a1);
+        if (c + 3 < nc) fetch(c + 3, a1);
+      }
+    }
+    if (norms) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        nn[b] += __shfl_xor(nn[b], 16, 64);
+        nn[b] += __shfl_xor(nn[b], 32, 64);
+        if (kc == 0) sN[wave * 32 + b * 16 + li] = sqrtf(nn[b] * 1.001f);
+      }
+    }
+    // rows of this lane's accumulator entries: wave * 32 + 16 b + 4 kc + r
+    const int rl = wave * 32 + kc * 4;
+#pragma unroll
+    for (int j = 0; j < QN; ++j) {
+      float v = -INFINITY;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (rl + 16 * b + r < rows) v = fmaxf(v, acc[b][j][r]);
+      v = rows_max(v);
+      if (kc == 0) sM[wave * QN * QB + j * QB + li] = v;
+    }
+    __syncthreads();
+    if (norms) write_norm_max<TILE>(sN, rows, tile, ws);
+    if (tid < QN * QB && q0 + tid < ws.mq) {
+      float v = sM[tid];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) v = fmaxf(v, sM[w * QN * QB + tid]);
+      ws.tmax[tmax_at(ws, q0 + tid, tile)] = v;
+    }
   }
 }
 
@@ -637,12 +891,25 @@ __device__ inline double group_dot_bf16(const double* qd, const uint16_t* __rest
 __device__ inline double group_dot_f32(const double* qd, const float* __restrict__ row, int d,
                                        int l8) {
   double p0 = 0.0, p1 = 0.0;
-  for (int k = l8 * 8; k < d; k += 64)
+  const int nch = d >> 3;
+  for (int c0 = l8; c0 < nch; c0 += 48) {
+    float4u v[6][2];
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      p0 = fma(qd[k + e], (double)row[k + e], p0);
-      p1 = fma(qd[k + e + 1], (double)row[k + e + 1], p1);
-    }
+    for (int u = 0; u < 6; ++u)
+      if (c0 + 8 * u < nch) {
+        v[u][0] = *(const float4u*)(row + 8 * (c0 + 8 * u));
+        v[u][1] = *(const float4u*)(row + 8 * (c0 + 8 * u) + 4);
+      }
+#pragma unroll
+    for (int u = 0; u < 6; ++u)
+      if (c0 + 8 * u < nch)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const int k = 8 * (c0 + 8 * u) + e;
+          p0 = fma(qd[k], (double)v[u][e >> 2][e & 3], p0);
+          p1 = fma(qd[k + 1], (double)v[u][e >> 2][(e & 3) + 1], p1);
+        }
+  }
   double s = p0 + p1;
   s += __shfl_xor(s, 1, 64);
   s += __shfl_xor(s, 2, 64);
@@ -650,65 +917,208 @@ __device__ inline double group_dot_f32(const double* qd, const float* __restrict
   return s;
 }
 
-// One workgroup per query: the rows of the listed tiles go to 32 groups of 8
-// lanes; a row is rescored canonically (by the group's first lane) unless its
-// group dot plus 2^-40 |q| N_t (a bound on the difference of the two dots,
-// with room) stays below L.  (Max, lowest index) over the rescored rows is
-// the result; its float32 rounding goes through the thresholds.
-__global__ void __launch_bounds__(256) lk_select(const float* __restrict__ queries, int d,
-                                                 const void* __restrict__ cache, int cache_bf16,
-                                                 int64_t n, int tr, Thresholds th, LookupWs ws,
-                                                 int64_t* __restrict__ idx_out,
-                                                 float* __restrict__ sim_out,
-                                                 int32_t* __restrict__ k_out) {
-  __shared__ double qd[MAX_D];
-  __shared__ double red[4];
-  __shared__ double rs[4];
-  __shared__ int64_t ri[4];
-  const int q = blockIdx.x;
-  double qq = 0.0;
-  for (int k = threadIdx.x; k < d; k += 256) {
-    const double v = (double)queries[(int64_t)q * d + k];
+// Canonical score of one row by a wave: the products (exact in float64) go to
+// LDS in parallel, the left-to-right sum runs over them.  The serial part is
+// one addition per element (a lane that also loads, converts and multiplies
+// takes three times as long).
+__device__ inline double canon_wave(const double* qd, const void* __restrict__ row, int bf, int d,
+                                    double* prod) {
+  const int lane = threadIdx.x & 63;
+  for (int c = lane; c * 8 < d; c += 64) {
+    float v[8];
+    if (bf) {
+      const uint4 w = *(const uint4*)((const uint16_t*)row + c * 8);
+      const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[2 * e] = __uint_as_float(u[e] << 16);
+        v[2 * e + 1] = __uint_as_float(u[e] & 0xFFFF0000u);
+      }
+    } else {
+      const float4u w0 = *(const float4u*)((const float*)row + c * 8);
+      const float4u w1 = *(const float4u*)((const float*)row + c * 8 + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = w0[e];
+        v[4 + e] = w1[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) prod[c * 8 + e] = qd[c * 8 + e] * (double)v[e];
+  }
+  // LDS operations of one wave complete in order; the fence keeps the compiler from
+  // moving the reads up
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  double s = 0.0;
+  for (int k = 0; k < d; k += 8) {
+    double2 p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[e] = *(const double2*)&prod[k + 2 * e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s = __dadd_rn(s, p[e].x);
+      s = __dadd_rn(s, p[e].y);
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  return s;
+}
+
+// The end of a lookup, one workgroup of FT threads per query: the rows of the
+// listed tiles go to groups of 8 lanes; a row is rescored canonically unless
+// its group dot plus 2^-40 |q| N_t (a bound on the difference of the two dots,
+// with room) stays below L.  (Max, lowest index) over the rescored rows is the
+// result; its float32 rounding goes through the thresholds.  Rows to rescore
+// are collected (up to SURV) and taken by whole waves; past that each group's
+// first lane sums its own (caches with many equal rows).
+// FUSED: the workgroup also computes the query's margin E (as lk_prep), its
+// lower bound L and its tile list from the scan's output, FT * FIN_PER tiles
+// at most, so a lookup over up to 2 M rows is a scan and this kernel (100 k
+// rows, one query: 38 us of lk_prep, lk_bound, lk_mark and a 256-thread
+// lk_select against 19 us).  1024 threads rescan a 128-row tile in one round;
+// calls of more than 256 queries take 256 threads, four workgroups per CU.
+constexpr int FIN_PER = 16;   // tiles per thread
+constexpr int SURV = 256;
+__host__ __device__ inline int fin_waves(int ft, int d) {  // waves with a product row in LDS
+  const int fit = 98304 / (d * 8);
+  return fit < ft / 64 ? fit : ft / 64;
+}
+
+template <int FT, bool FUSED>
+__global__ void __launch_bounds__(FT) lk_finish(const float* __restrict__ queries, int d,
+                                                const void* __restrict__ cache, int cache_bf16,
+                                                int64_t n, int tr, Thresholds th, LookupWs ws,
+                                                int64_t* __restrict__ idx_out,
+                                                float* __restrict__ sim_out,
+                                                int32_t* __restrict__ k_out) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NWV = FT / 64;
+  __shared__ double red[3][NWV];
+  __shared__ double rs[NWV];
+  __shared__ int64_t ri[NWV];
+  __shared__ int32_t surv[SURV];
+  __shared__ int s_cnt, s_surv;
+  const int nprod = fin_waves(FT, d);
+  double* qd = (double*)smem;                        // [d]
+  double* prods = qd + d;                            // [nprod][d]
+  uint16_t* slist = (uint16_t*)(prods + (size_t)nprod * d);  // [T] (FUSED)
+  const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float M[FUSED ? FIN_PER : 1], N[FUSED ? FIN_PER : 1];
+  if (FUSED)
+#pragma unroll
+    for (int u = 0; u < FIN_PER; ++u) {
+      const int t = tid + u * FT;
+      M[u] = t < ws.T ? ws.tmax[tmax_at(ws, q, t)] : -INFINITY;
+      N[u] = t < ws.T ? ws.nmax[t] : 0.f;
+    }
+  double e2 = 0.0, nb = 0.0, qq = 0.0;
+  for (int k = tid; k < d; k += FT) {
+    const float f = queries[(int64_t)q * d + k];
+    const double v = (double)f;
     qd[k] = v;
     qq += v * v;
+    if (FUSED) {
+      const double vb = (double)bf16_to_f32(f32_to_bf16_rne(f));
+      e2 += (v - vb) * (v - vb);
+      nb += vb * vb;
+    }
   }
-  const double qn = sqrt(block_sum_256(qq, red)) * (1.0 + 0x1p-40);
-  const double L = dkey_inv(ws.Lkey[q]);
-  const int64_t rows = (int64_t)ws.cnt[q] * tr;
+  if (tid == 0) s_cnt = s_surv = 0;
+  auto block_sum3 = [&]() {
+    for (int o = 32; o > 0; o >>= 1) {
+      qq += __shfl_xor(qq, o, 64);
+      if (FUSED) {
+        e2 += __shfl_xor(e2, o, 64);
+        nb += __shfl_xor(nb, o, 64);
+      }
+    }
+    if (lane == 0) {
+      red[0][wave] = qq;
+      red[1][wave] = e2;
+      red[2][wave] = nb;
+    }
+    __syncthreads();
+    qq = e2 = nb = 0.0;
+    for (int w = 0; w < NWV; ++w) {
+      qq += red[0][w];
+      e2 += red[1][w];
+      nb += red[2][w];
+    }
+  };
+  block_sum3();
+  const double qn = sqrt(qq) * (1.0 + 0x1p-40);
+  double L;
+  int cnt;
   const int32_t* lst = ws.list + (int64_t)q * ws.T;
-  const int g = threadIdx.x >> 3, l8 = threadIdx.x & 7;
+  if (FUSED) {
+    const double accb = 2.0 * d * 0x1p-24 + d * 0x1p-52;
+    double E = cache_bf16 ? sqrt(e2) + accb * sqrt(nb) : accb * sqrt(qq);
+    E = E * (1.0 + 0x1p-20) + 0x1p-60;
+    L = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < FIN_PER; ++u)
+      if (tid + u * FT < ws.T) L = fmax(L, lower_d(M[u], N[u], E));
+    for (int o = 32; o > 0; o >>= 1) L = fmax(L, __shfl_xor(L, o, 64));
+    if (lane == 0) rs[wave] = L;
+    __syncthreads();
+    for (int w = 0; w < NWV; ++w) L = fmax(L, rs[w]);
+#pragma unroll
+    for (int u = 0; u < FIN_PER; ++u)
+      if (tid + u * FT < ws.T && upper_d(M[u], N[u], E) >= L)
+        slist[atomicAdd(&s_cnt, 1)] = (uint16_t)(tid + u * FT);
+    __syncthreads();
+    cnt = s_cnt;
+  } else {
+    L = dkey_inv(ws.Lkey[q]);
+    cnt = ws.cnt[q];
+  }
+  const int64_t rows = (int64_t)cnt * tr;
+  const int g = tid >> 3, l8 = tid & 7;
   double bs = -INFINITY;
   int64_t bi = INT64_MAX;
-  for (int64_t i = g; i < rows; i += 32) {
-    const int tt = lst[i / tr];
+  for (int64_t i = g; i < rows; i += FT / 8) {
+    const int li = (int)(i / tr);
+    const int tt = FUSED ? (int)slist[li] : lst[li];
     const int64_t row = (int64_t)tt * tr + i % tr;
     if (row >= n) continue;  // uniform in the group
     const double tol = 0x1p-40 * qn * (double)ws.nmax[tt] + 0x1p-1000;
-    if (cache_bf16) {
-      const uint16_t* c = (const uint16_t*)cache + row * (int64_t)d;
-      if (group_dot_bf16(qd, c, d, l8) + tol >= L && l8 == 0)
-        better(bs, bi, canon_bf16(qd, c, d), row);
-    } else {
-      const float* c = (const float*)cache + row * (int64_t)d;
-      if (group_dot_f32(qd, c, d, l8) + tol >= L && l8 == 0)
-        better(bs, bi, canon_f32(qd, c, d), row);
+    const uint16_t* cb = (const uint16_t*)cache + row * (int64_t)d;
+    const float* cf = (const float*)cache + row * (int64_t)d;
+    const double fast = cache_bf16 ? group_dot_bf16(qd, cb, d, l8) : group_dot_f32(qd, cf, d, l8);
+    if (fast + tol >= L && l8 == 0) {
+      const int at = atomicAdd(&s_surv, 1);
+      if (at < SURV)
+        surv[at] = (int32_t)row;  // n < 2^31
+      else
+        better(bs, bi, cache_bf16 ? canon_bf16(qd, cb, d) : canon_f32(qd, cf, d), row);
     }
   }
+  __syncthreads();
+  const int ns = min(s_surv, SURV);
+  if (wave < nprod)
+    for (int i = wave; i < ns; i += nprod) {
+      const int64_t row = surv[i];
+      const void* c = cache_bf16 ? (const void*)((const uint16_t*)cache + row * (int64_t)d)
+                                 : (const void*)((const float*)cache + row * (int64_t)d);
+      better(bs, bi, canon_wave(qd, c, cache_bf16, d, prods + (size_t)wave * d), row);
+    }
   // (max score, lowest index) reduction
   for (int o = 32; o > 0; o >>= 1) {
     const double s2 = __shfl_xor(bs, o, 64);
     const int64_t i2 = __shfl_xor(bi, o, 64);
     better(bs, bi, s2, i2);
   }
-  if ((threadIdx.x & 63) == 0) {
-    rs[threadIdx.x >> 6] = bs;
-    ri[threadIdx.x >> 6] = bi;
+  __syncthreads();  // rs may still hold the bounds
+  if (lane == 0) {
+    rs[wave] = bs;
+    ri[wave] = bi;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     double s = rs[0];
     int64_t i = ri[0];
-    for (int w = 1; w < 4; ++w) better(s, i, rs[w], ri[w]);
+    for (int w = 1; w < NWV; ++w) better(s, i, rs[w], ri[w]);
     if (n == 0 || i == INT64_MAX) {
       idx_out[q] = -1;
       sim_out[q] = -INFINITY;
@@ -815,11 +1225,44 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
   LookupWs ws{(uint16_t*)(w + p.off_qbf), (double*)(w + p.off_E), (float*)(w + p.off_tmax),
               (float*)(w + p.off_nmax),   (uint64_t*)(w + p.off_Lkey), (int32_t*)(w + p.off_cnt),
               (int32_t*)(w + p.off_list), mq_pad, dp, T};
-  hipLaunchKernelGGL(lk_prep, dim3(mq_pad), dim3(256), 0, s, queries, m, mq_pad, d, dp, bf, ws.qbf,
-                     ws.E, ws);
-  NV_LAUNCH_CHECK("lk_prep");
+  // bounds, tile list and rescan in one kernel for up to FIN_PER tiles a thread
+  const int ft = m <= 256 ? 1024 : 256;
+  const bool fused = T <= ft * FIN_PER;
+  // many queries stay in registers while the rows stream: past MANY_M queries
+  const bool many = rr && m > MANY_M;
+  // the scan converts one or two queries itself (every workgroup does: 8 queries
+  // over 1 M rows 260 us against 243 with lk_prep's copy)
+  const bool convert = rr && !many && m <= 2;
+  if (!fused || (bf && !convert)) {
+    hipLaunchKernelGGL(lk_prep, dim3(mq_pad), dim3(256), 0, s, queries, m, mq_pad, d, dp, bf, ws.qbf,
+                       ws.E, ws);
+    NV_LAUNCH_CHECK("lk_prep");
+  }
   if (T > 0) {
-    if (rr) {
+    if (many) {
+      const size_t lds = (size_t)MANY_R * 16 * dp * 2 + 8 * 4;
+      const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d);
+      const uint16_t* cb = (const uint16_t*)cache;
+      const int nbw = m > 128 ? 4 : 2;
+      const dim3 grid((unsigned)std::min(T, 256), (unsigned)ceil_div(m, 64 * nbw));
+#define NV_MANY1(ns, w)                                                                         \
+  {                                                                                             \
+    NV_HIP_TRY(hipFuncSetAttribute((const void*)lk_scan_many<ns, w>,                            \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));      \
+    hipExtLaunchKernelGGL((lk_scan_many<ns, w>), grid, dim3(256), (uint32_t)lds, s, ev.a, ev.b, \
+                          0u, cb, n, (int)d, (int)m, ws);                                       \
+  }
+      switch (dp / 32) {
+#define NV_MANY(ns) \
+  case ns:          \
+    if (nbw == 4)   \
+      NV_MANY1(ns, 4) else NV_MANY1(ns, 2) break;
+        NV_MANY(4) NV_MANY(8) NV_MANY(12) NV_MANY(16) NV_MANY(20) NV_MANY(24)
+#undef NV_MANY
+#undef NV_MANY1
+      }
+      NV_LAUNCH_CHECK("lk_scan_many");
+    } else if (rr) {
       const size_t lds = (size_t)3 * QB * dp * 2 + (size_t)2 * 4 * QB * 4 + RR_TILE * 4;
       const void* fn = nullptr;
       switch (dp / 32) {
@@ -834,7 +1277,7 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
 #define NV_RR(ns)                                                                          \
   case ns:                                                                                 \
     hipExtLaunchKernelGGL(lk_scan_bf16<ns>, dim3(T), dim3(256), (uint32_t)lds, s, ev.a, ev.b, \
-                          0u, cb, n, (int)d, (int)m, ws);                                  \
+                          0u, cb, n, (int)d, (int)m, ws, convert ? queries : (const float*)nullptr); \
     break;
         NV_RR(4) NV_RR(8) NV_RR(12) NV_RR(16) NV_RR(20) NV_RR(24)
 #undef NV_RR
@@ -850,21 +1293,46 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
       NV_LAUNCH_CHECK("lk_scan_bf16_wide");
     } else {
       const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 4.0 * (double)n * d);
-      hipExtLaunchKernelGGL(lk_scan_f32, dim3(T), dim3(256), 0u, s, ev.a, ev.b, 0u,
-                            (const float*)cache, n, (int)d, queries, (int)m, ws);
+      // two query blocks per pass where they fit: each pass reads the rows
+      auto lds_of = [&](int qn) {
+        return (size_t)qn * QB * f32_qrow(d) * 4 + (size_t)8 * qn * QB * 4 + TILE * 4;
+      };
+      const bool two = m > QB && lds_of(2) <= 160 * 1024;
+      const size_t lds = lds_of(two ? 2 : 1);
+      NV_HIP_TRY(hipFuncSetAttribute(
+          two ? (const void*)lk_scan_f32<2> : (const void*)lk_scan_f32<1>,
+          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      if (two)
+        hipExtLaunchKernelGGL(lk_scan_f32<2>, dim3(T), dim3(F32_T), (uint32_t)lds, s, ev.a, ev.b, 0u,
+                              (const float*)cache, n, (int)d, queries, (int)m, ws);
+      else
+        hipExtLaunchKernelGGL(lk_scan_f32<1>, dim3(T), dim3(F32_T), (uint32_t)lds, s, ev.a, ev.b, 0u,
+                              (const float*)cache, n, (int)d, queries, (int)m, ws);
       NV_LAUNCH_CHECK("lk_scan_f32");
     }
   }
-  if (T > 0) {
+  if (!fused) {
     const dim3 grid((unsigned)ceil_div(T, BCH), (unsigned)(mq_pad / QB));
     hipLaunchKernelGGL(lk_bound, grid, dim3(256), 0, s, (int)m, ws);
     NV_LAUNCH_CHECK("lk_bound");
     hipLaunchKernelGGL(lk_mark, grid, dim3(256), 0, s, (int)m, ws);
     NV_LAUNCH_CHECK("lk_mark");
   }
-  hipLaunchKernelGGL(lk_select, dim3(m), dim3(256), 0, s, queries, d, cache, bf, n, tr, th, ws,
-                     idx_out, sim_out, k_out);
-  NV_LAUNCH_CHECK("lk_select");
+  const size_t flds = align_up((size_t)d * 8 * (1 + fin_waves(ft, d)) + (fused ? (size_t)T * 2 : 0), 16);
+#define NV_FIN(t, f)                                                                             \
+  {                                                                                              \
+    NV_HIP_TRY(hipFuncSetAttribute((const void*)lk_finish<t, f>,                                 \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)flds));      \
+    hipLaunchKernelGGL((lk_finish<t, f>), dim3(m), dim3(t), (uint32_t)flds, s, queries, d, cache, \
+                       bf, n, tr, th, ws, idx_out, sim_out, k_out);                              \
+  }
+  if (ft == 1024) {
+    if (fused) NV_FIN(1024, true) else NV_FIN(1024, false)
+  } else {
+    if (fused) NV_FIN(256, true) else NV_FIN(256, false)
+  }
+#undef NV_FIN
+  NV_LAUNCH_CHECK("lk_finish");
   return NV_OK;
 }
 
