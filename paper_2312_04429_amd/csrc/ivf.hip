@@ -214,64 +214,89 @@ __global__ void __launch_bounds__(256) list_normalise_k(const double* __restrict
   }
 }
 
-// Canonical scores of up to 256 consecutive stored rows against one float32
-// query, one row per thread.  The rows pass through LDS in slices of 32 words
-// (64 bf16 or 32 f32 values per row): every slice is read with coalesced
-// 16-byte loads, and each thread then adds its row's products in k order from
-// a conflict-free padded layout (row stride 33 words).
-constexpr int SLICE_W = 32;
-
-__device__ inline double canon_rows_block(const float* __restrict__ q, const char* __restrict__ rows,
-                                          int nrows, int bf, int d, uint32_t (*tile)[SLICE_W + 1],
-                                          float* qs) {
-  const int t = threadIdx.x;
-  const int row_words = d * (bf ? 2 : 4) / 4;
-  double s = 0.0;
-  for (int w0 = 0; w0 < row_words; w0 += SLICE_W) {
-    const int ws = min(SLICE_W, row_words - w0);       // words in this slice (multiple of 4)
-    for (int c = t; c < 256 * (SLICE_W / 4); c += 256) {
-      const int r = c / (SLICE_W / 4), part = c % (SLICE_W / 4);
-      if (r < nrows && part * 4 < ws) {
-        const u32x4 v = *(const u32x4*)((const uint32_t*)rows + (int64_t)r * row_words + w0 +
-                                         part * 4);
-        tile[r][part * 4] = v[0];
-        tile[r][part * 4 + 1] = v[1];
-        tile[r][part * 4 + 2] = v[2];
-        tile[r][part * 4 + 3] = v[3];
-      }
-    }
-    const int k0 = bf ? 2 * w0 : w0;
-    const int nk = bf ? 2 * ws : ws;
-    if (t < nk) qs[t] = q[k0 + t];
-    __syncthreads();
-    if (t < nrows) {
-      if (bf) {
-        for (int w = 0; w < ws; ++w) {
-          const uint32_t v = tile[t][w];
-          s += (double)qs[2 * w] * (double)__uint_as_float(v << 16);
-          s += (double)qs[2 * w + 1] * (double)__uint_as_float(v & 0xFFFF0000u);
-        }
-      } else {
-        for (int w = 0; w < ws; ++w) s += (double)qs[w] * (double)__uint_as_float(tile[t][w]);
-      }
-    }
-    __syncthreads();
-  }
-  return s;
+// Doubles of the query in LDS, zero padded to whole 64-value slices.
+__host__ __device__ inline int q_padded(int d) { return (d + 63) / 64 * 64; }
+__device__ inline void load_query(double* qd, const float* __restrict__ q, int d) {
+  for (int k = threadIdx.x; k < q_padded(d); k += blockDim.x) qd[k] = k < d ? (double)q[k] : 0.0;
 }
 
-// cs[j][l]: canonical score of query j against centroid l (256 centroids per block)
+// cs[j][l]: canonical score of query j against centroid l, 64 centroids per
+// block of four waves.  The serial part of a canonical sum is one float64
+// addition per element; everything else is shared out: in slices of 64 values,
+// all four waves load, convert and multiply (exact in float64) into one LDS
+// buffer while lane r of the first wave adds row r's products of the previous
+// slice from the other.  With one thread per row doing all of it, 1024
+// centroids took 52 us (28 without its barriers).
+constexpr int PROW = 66;  // products per LDS row (64, and room against bank conflicts)
+
 __global__ void __launch_bounds__(256) cent_scores_k(const float* __restrict__ q, int d,
                                                      const void* __restrict__ cents, int bf,
                                                      int L, double* __restrict__ cs) {
-  __shared__ uint32_t tile[256][SLICE_W + 1];
-  __shared__ float qs[2 * SLICE_W];
-  const int j = blockIdx.y, l0 = blockIdx.x * 256;
-  const int nrows = min(256, L - l0);
-  const double v = canon_rows_block(q + (int64_t)j * d,
-                                    (const char*)cents + (int64_t)l0 * d * (bf ? 2 : 4), nrows,
-                                    bf, d, tile, qs);
-  if ((int)threadIdx.x < nrows) cs[(int64_t)j * L + l0 + threadIdx.x] = v;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* qd = (double*)smem;             // [q_padded(d)]
+  double* prod = qd + q_padded(d);        // [2][64][PROW]
+  const int j = blockIdx.y, l0 = blockIdx.x * 64, t = threadIdx.x;
+  const int nrows = min(64, L - l0);
+  const int slices = q_padded(d) / 64;
+  // thread t: row t / 4, 16 values from (t % 4) * 16 of every slice
+  const int row = t >> 2, k0 = (t & 3) * 16;
+  const bool live = row < nrows;
+  float v[2][16];
+  auto fetch = [&](int sl, float(&x)[16]) {
+    const int k = sl * 64 + k0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      u32x4 w0 = {0u, 0u, 0u, 0u}, w1 = {0u, 0u, 0u, 0u};
+      if (live && k + 8 * h < d) {  // d is a multiple of 8
+        if (bf) {
+          w0 = *(const u32x4*)((const uint16_t*)cents + (int64_t)(l0 + row) * d + k + 8 * h);
+        } else {
+          const float* c = (const float*)cents + (int64_t)(l0 + row) * d + k + 8 * h;
+          w0 = *(const u32x4*)c;
+          w1 = *(const u32x4*)(c + 4);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t a = w0[e], b = w1[e];
+        if (bf) {
+          x[8 * h + 2 * e] = __uint_as_float(a << 16);
+          x[8 * h + 2 * e + 1] = __uint_as_float(a & 0xFFFF0000u);
+        } else {
+          x[8 * h + e] = __uint_as_float(a);
+          x[8 * h + 4 + e] = __uint_as_float(b);
+        }
+      }
+    }
+  };
+  fetch(0, v[0]);
+  fetch(1, v[1]);
+  load_query(qd, q + (int64_t)j * d, d);
+  __syncthreads();
+  double s = 0.0;
+  auto turn = [&](int sl, float(&x)[16]) {
+    if (sl < slices) {
+      double* p = prod + (sl & 1) * 64 * PROW + row * PROW + k0;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) p[e] = qd[sl * 64 + k0 + e] * (double)x[e];
+      fetch(sl + 2, x);
+    }
+    if (sl > 0 && t < 64) {
+      const double2* p = (const double2*)(prod + ((sl - 1) & 1) * 64 * PROW + t * PROW);
+#pragma unroll 8
+      for (int e = 0; e < 32; ++e) {
+        const double2 y = p[e];
+        s = __dadd_rn(s, y.x);
+        s = __dadd_rn(s, y.y);
+      }
+    }
+    __syncthreads();
+  };
+  for (int sl = 0; sl <= slices; sl += 2) {
+    turn(sl, v[0]);
+    if (sl + 1 <= slices) turn(sl + 1, v[1]);
+  }
+  if (t < nrows) cs[(int64_t)j * L + l0 + t] = s;
 }
 
 // the nprobe best lists of query j in rank order (higher score first, lower
@@ -332,14 +357,24 @@ __global__ void __launch_bounds__(256) top_lists_k(const double* __restrict__ cs
         atomicAdd(&hist[(key[e] >> (8 * byte)) & 255], 1);
     }
     __syncthreads();
-    if (t == 0) {
-      int acc = 0, b = 255;
-      for (; b > 0; --b) {
-        if (acc + hist[b] >= need) break;
-        acc += hist[b];
+    // thread t's bin is the one where the count of larger-or-equal keys passes
+    // `need` (a suffix sum: within waves by shuffles, then over waves; one thread
+    // walking the bins took 6 us a byte)
+    {
+      const int own = hist[t];
+      int suf = own;
+      const int lane = t & 63;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_down(suf, o, 64);
+        if (lane + o < 64) suf += x;
       }
-      need_sh = need - acc;
-      kstar_sh = prefix | ((uint64_t)b << (8 * byte));
+      if (lane == 0) scan_sh[t >> 6] = suf;
+      __syncthreads();
+      for (int w = (t >> 6) + 1; w < 4; ++w) suf += scan_sh[w];
+      if (suf >= need && suf - own < need) {
+        need_sh = need - (suf - own);
+        kstar_sh = prefix | ((uint64_t)t << (8 * byte));
+      }
     }
     __syncthreads();
     need = need_sh;
@@ -383,45 +418,169 @@ __global__ void __launch_bounds__(256) top_lists_k(const double* __restrict__ cs
   }
 }
 
-// best probed row per (query, probe, chunk of 256 list positions)
-__global__ void __launch_bounds__(256) probe_scan_k(const float* __restrict__ q, int d,
-                                                    const void* __restrict__ lrows, int bf,
-                                                    const int64_t* __restrict__ perm,
-                                                    const int64_t* __restrict__ off,
-                                                    const int32_t* __restrict__ probed,
-                                                    int nprobe, int chunks,
-                                                    double* __restrict__ ps,
-                                                    int64_t* __restrict__ pi) {
-  __shared__ uint32_t tile[256][SLICE_W + 1];
-  __shared__ float qs[2 * SLICE_W];
-  __shared__ double rs[256];
-  __shared__ int64_t ri[256];
-  const int jp = blockIdx.x, ch = blockIdx.y, t = threadIdx.x;
+// Best probed row per (query, probe, chunk of 256 list positions).  Groups of 8
+// lanes take float64 dots of the rows in another summation order, each within
+// tol = 2^-40 |q| |c| of the canonical score (2 d 2^-53 |q| |c| at most, d <=
+// 2048, and room for the norms' own rounding); the rows that can still hold
+// the block's best canonical score (dot + tol reaches the largest dot - tol)
+// are summed canonically, usually one: exact products into LDS by its wave,
+// then the additions in order.  The result is the best (score, lowest row) of
+// the block, as if every row had been summed (one query, 32 lists of about a
+// thousand rows: 54 us with a canonical sum per row against 29).
+constexpr int PS_T = 512;
+
+__global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q, int d,
+                                                     const void* __restrict__ lrows, int bf,
+                                                     const int64_t* __restrict__ perm,
+                                                     const int64_t* __restrict__ off,
+                                                     const int32_t* __restrict__ probed,
+                                                     int nprobe, int chunks,
+                                                     double* __restrict__ ps,
+                                                     int64_t* __restrict__ pi) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int NWV = PS_T / 64;
+  double* qd = (double*)smem;                     // [q_padded(d)]
+  double* prods = qd + q_padded(d);               // [NWV / 2][q_padded(d)]
+  __shared__ double fast[256], tols[256];
+  __shared__ double red[NWV], rs[NWV];
+  __shared__ int64_t ri[NWV];
+  __shared__ int surv[256];
+  __shared__ int n_surv;
+  const int jp = blockIdx.x, ch = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int j = jp / nprobe;
   const int l = probed[jp];
   const int64_t p0 = off[l] + (int64_t)ch * 256;
   const int nrows = (int)max<int64_t>(0, min<int64_t>(256, off[l + 1] - p0));
+  if (nrows == 0) {  // past the list's end
+    if (t == 0) {
+      ps[(int64_t)jp * chunks + ch] = -INFINITY;
+      pi[(int64_t)jp * chunks + ch] = -1;
+    }
+    return;
+  }
+  const char* rows = (const char*)lrows + p0 * d * (bf ? 2 : 4);
+  load_query(qd, q + (int64_t)j * d, d);
+  if (t == 0) n_surv = 0;
+  __syncthreads();
+  double qq = 0.0;
+  for (int k = t; k < d; k += PS_T) qq = fma(qd[k], qd[k], qq);
+  for (int o = 32; o > 0; o >>= 1) qq += __shfl_xor(qq, o, 64);
+  if (lane == 0) red[wave] = qq;
+  // 64 groups of 8 lanes; lane l8 takes chunks l8, l8 + 8, ... of 8 values
+  const int g = t >> 3, l8 = t & 7, nch = d >> 3;
+  for (int r = g; r < nrows; r += PS_T / 8) {
+    double a0 = 0.0, a1 = 0.0;
+    float nn = 0.f;
+    for (int c0 = l8; c0 < nch; c0 += 48) {
+      u32x4 v[6][2];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const int c = c0 + 8 * u;
+        if (c < nch) {
+          if (bf) {
+            v[u][0] = *(const u32x4*)((const uint16_t*)rows + (int64_t)r * d + c * 8);
+          } else {
+            v[u][0] = *(const u32x4*)((const float*)rows + (int64_t)r * d + c * 8);
+            v[u][1] = *(const u32x4*)((const float*)rows + (int64_t)r * d + c * 8 + 4);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const int c = c0 + 8 * u;
+        if (c >= nch) break;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x, y;
+          if (bf) {
+            const uint32_t w = v[u][0][e];
+            x = __uint_as_float(w << 16);
+            y = __uint_as_float(w & 0xFFFF0000u);
+          } else {
+            const uint32_t w0 = v[u][e >> 1][2 * (e & 1)], w1 = v[u][e >> 1][2 * (e & 1) + 1];
+            x = __uint_as_float(w0);
+            y = __uint_as_float(w1);
+          }
+          nn = fmaf(x, x, nn);
+          nn = fmaf(y, y, nn);
+          a0 = fma(qd[c * 8 + 2 * e], (double)x, a0);
+          a1 = fma(qd[c * 8 + 2 * e + 1], (double)y, a1);
+        }
+      }
+    }
+    double s = a0 + a1;
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    s += __shfl_xor(s, 4, 64);
+    nn += __shfl_xor(nn, 1, 64);
+    nn += __shfl_xor(nn, 2, 64);
+    nn += __shfl_xor(nn, 4, 64);
+    if (l8 == 0) {
+      fast[r] = s;
+      tols[r] = sqrt((double)nn * 1.001 + 0x1p-120);  // at least the row's norm
+    }
+  }
+  __syncthreads();
+  qq = 0.0;
+  for (int w = 0; w < NWV; ++w) qq += red[w];
+  const double scale = 0x1p-40 * sqrt(qq) * (1.0 + 0x1p-40);
+  // the block's best canonical score is at least the largest dot - tol
+  double lo = -INFINITY;
+  if (t < nrows) lo = fast[t] - (scale * tols[t] + 0x1p-1000);
+  for (int o = 32; o > 0; o >>= 1) lo = fmax(lo, __shfl_xor(lo, o, 64));
+  if (lane == 0) rs[wave] = lo;
+  __syncthreads();
+  for (int w = 0; w < NWV; ++w) lo = fmax(lo, rs[w]);
+  // a dot that is not a number is summed canonically too
+  if (t < nrows && !(fast[t] + (scale * tols[t] + 0x1p-1000) < lo)) surv[atomicAdd(&n_surv, 1)] = t;
+  __syncthreads();
   double bs = -INFINITY;
   int64_t bi = -1;
-  if (nrows > 0) {
-    bs = canon_rows_block(q + (int64_t)j * d, (const char*)lrows + p0 * d * (bf ? 2 : 4), nrows,
-                          bf, d, tile, qs);
-    if (t < nrows) bi = perm[p0 + t];
-    else bs = -INFINITY;
-  }
-  rs[t] = bs;
-  ri[t] = bi;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (t < w && ri[t + w] >= 0 && (ri[t] < 0 || better_pair(rs[t + w], ri[t + w], rs[t], ri[t]))) {
-      rs[t] = rs[t + w];
-      ri[t] = ri[t + w];
+  const int ns = n_surv;
+  if (wave < NWV / 2) {
+    double* prod = prods + (size_t)wave * q_padded(d);
+    for (int i = wave; i < ns; i += NWV / 2) {
+      const int r = surv[i];
+      for (int c = lane; c < nch; c += 64)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = c * 8 + e;
+          const float x = bf ? __uint_as_float((uint32_t)((const uint16_t*)rows)[(int64_t)r * d + k] << 16)
+                             : ((const float*)rows)[(int64_t)r * d + k];
+          prod[k] = qd[k] * (double)x;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      double s = 0.0;
+      for (int k = 0; k < d; k += 8)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double2 y = *(const double2*)&prod[k + 2 * e];
+          s = __dadd_rn(s, y.x);
+          s = __dadd_rn(s, y.y);
+        }
+      __builtin_amdgcn_wave_barrier();
+      const int64_t row = perm[p0 + r];
+      if (bi < 0 || better_pair(s, row, bs, bi)) {
+        bs = s;
+        bi = row;
+      }
     }
-    __syncthreads();
   }
+  __syncthreads();  // rs held the bounds
+  if (lane == 0) {
+    rs[wave] = bs;
+    ri[wave] = bi;
+  }
+  __syncthreads();
   if (t == 0) {
-    ps[(int64_t)jp * chunks + ch] = rs[0];
-    pi[(int64_t)jp * chunks + ch] = ri[0];
+    for (int w = 1; w < NWV / 2; ++w)
+      if (ri[w] >= 0 && (bi < 0 || better_pair(rs[w], ri[w], bs, bi))) {
+        bs = rs[w];
+        bi = ri[w];
+      }
+    ps[(int64_t)jp * chunks + ch] = bs;
+    pi[(int64_t)jp * chunks + ch] = bi;
   }
 }
 
@@ -651,13 +810,21 @@ extern "C" int32_t nv_ivf_search(const float* queries, int32_t m, int32_t d, con
   double* ps = (double*)after;
   int64_t* pi = (int64_t*)(after + align_up((size_t)m * nprobe * chunks * 8, 256));
   const int bf = c_dtype == NV_BF16;
-  hipLaunchKernelGGL(cent_scores_k, dim3((unsigned)ceil_div(L, 256), (unsigned)m), dim3(256), 0, s,
-                     queries, d, cents, bf, L, cs);
+  // at most 84 KB and 82 KB of LDS (d = 2048)
+  const size_t clds = (size_t)q_padded(d) * 8 + (size_t)2 * 64 * PROW * 8;
+  const size_t plds = (size_t)q_padded(d) * 8 * (1 + PS_T / 128);
+  NV_HIP_TRY(hipFuncSetAttribute((const void*)cent_scores_k,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)clds));
+  NV_HIP_TRY(hipFuncSetAttribute((const void*)probe_scan_k,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)plds));
+  hipLaunchKernelGGL(cent_scores_k, dim3((unsigned)ceil_div(L, 64), (unsigned)m), dim3(256),
+                     (uint32_t)clds, s, queries, d, cents, bf, L, cs);
   NV_LAUNCH_CHECK("cent_scores_k");
   hipLaunchKernelGGL(top_lists_k, dim3((unsigned)m), dim3(256), 0, s, (const double*)cs, L, nprobe,
                      probed);
   NV_LAUNCH_CHECK("top_lists_k");
-  hipLaunchKernelGGL(probe_scan_k, dim3((unsigned)(m * nprobe), (unsigned)chunks), dim3(256), 0, s,
+  hipLaunchKernelGGL(probe_scan_k, dim3((unsigned)(m * nprobe), (unsigned)chunks), dim3(PS_T),
+                     (uint32_t)plds, s,
                      queries, d, ivf_rows, bf, perm, offsets, (const int32_t*)probed, nprobe,
                      chunks, ps, pi);
   NV_LAUNCH_CHECK("probe_scan_k");
