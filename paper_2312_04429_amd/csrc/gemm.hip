@@ -1714,15 +1714,16 @@ float wide_cost(const WideForm& w, const GemmArgs& g) {
 
 // The cheapest form, or -1 where the kernels below are the better choice: the
 // row-staged epilogue does not apply, or K is long enough over a grid small
-// enough that split K pays (about 10 us + 650 TFLOP/s with its reduction:
-// 2 x 16 x 16 1280 -> 1280 32.5 us against 39 to 46).  GEGLU combines its quads
-// in registers (forms 0 and 4) or, on small grids, from the staged rows.
+// enough that split K pays (about 16 us + 800 TFLOP/s with its reduction, inside
+// the network: the 2 x 16 x 16 1280 -> 1280 convolution 32 us against 39 to 46;
+// 512 x 1280 x 5120 26.5 us split, 20 unsplit).  GEGLU combines its quads in
+// registers (forms 0 and 4; from staged rows 512 x 10240 x 1280 takes 35 us).
 int wide_form(const GemmArgs& g) {
   if (!g.rows_ok) return -1;
   int best = -1;
   float cost = 1e30f;
   for (int i = 0; i < (int)(sizeof(WIDE) / sizeof(WIDE[0])); ++i) {
-    if (g.geglu && i != 0 && i != 4 && i != 7) continue;
+    if (g.geglu && i != 0 && i != 4) continue;
     const float c = wide_cost(WIDE[i], g);
     if (c < cost) {
       cost = c;
@@ -1731,7 +1732,7 @@ int wide_form(const GemmArgs& g) {
   }
   const bool can_split = g.partial && !g.ln_c1 && !g.geglu && g.K / 64 >= 20 &&
                          (size_t)2 * g.M * g.N * 4 <= g.partial_bytes;
-  if (can_split && 10.0f + 2.0f * (float)g.M * (float)g.N * (float)g.K / 650e6f < cost) return -1;
+  if (can_split && 16.0f + 2.0f * (float)g.M * (float)g.N * (float)g.K / 800e6f < cost) return -1;
   return best;
 }
 

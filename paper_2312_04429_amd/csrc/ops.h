@@ -30,7 +30,8 @@ struct GnArgs {
   const float* beta;
   int silu;
   float* part;           // [rows][part_chunks][G][2] chunk partials (scratch)
-  int part_chunks;       // chunk capacity per row of part (at least ceil(HW / 8))
+  int part_chunks;       // chunk capacity per row of part (at least ceil(HW / 8) + 1: the
+                         // last one holds the merged statistics)
   _Float16* out;         // [rows][HW][C1 + C2]
 };
 

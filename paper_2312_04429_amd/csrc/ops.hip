@@ -28,17 +28,16 @@ __device__ inline float load_cat(const _Float16* s1, int C1, const _Float16* s2,
   return c < C1 ? (float)s1[pix * C1 + c] : (float)s2[pix * C2 + (c - C1)];
 }
 
-// GroupNorm, deterministic and two-pass at every level, in two launches:
+// GroupNorm, deterministic and two-pass at every level, in three launches:
 //   gn_stats_k: one workgroup per (row, chunk of P pixels).  Threads own
 //     8-channel vectors (16-byte loads) of a phase of the chunk's pixels, held
 //     in registers for both passes (one sweep over memory); LDS folds phases,
 //     then channels into groups, in a fixed order.  Output per (row, chunk,
 //     group): mean and sum of squared deviations from it.
-//   gn_apply_k: one workgroup per (row, block of Q pixels).  It first merges
-//     the chunk partials of every group of its row with the pairwise (Chan)
-//     update over a fixed tree (every workgroup of the row gets identical
-//     statistics), builds per-channel scale and shift in LDS, then normalises,
-//     applies the affine map and the optional SiLU, 8 channels per thread.
+//   gn_merge_k: one workgroup per row merges the chunk partials of every group
+//     with the pairwise (Chan) update over a fixed tree.
+//   gn_apply_k: normalises, applies the affine map and the optional SiLU, 8
+//     channels per thread.
 constexpr int GN_MAXC = 4096;
 constexpr int GN_VPT = 16;  // 16-byte vectors per thread and vector slot in gn_stats_k
 
@@ -147,37 +146,13 @@ __device__ inline void chan_merge(double& n, double& mean, double& m2, double nb
   n = nn;
 }
 
-constexpr int GN_APT = 4;  // 16-byte vectors per thread in gn_apply_k (Q * nv <= 1024)
-
-__global__ void __launch_bounds__(256) gn_apply_k(GnArgs a, int nchunks, int Q) {
-  __shared__ float sc[GN_MAXC], sf[GN_MAXC];  // per-channel scale and shift
-  __shared__ float gm[256], gr[256];          // per-group mean, rstd
+// One workgroup per row: (mean, 1 / sqrt(var + eps)) of every group, merged from
+// the chunk partials (TPG threads per group, chunks strided over them, then a
+// fixed tree) and stored past them.
+__global__ void __launch_bounds__(256) gn_merge_k(GnArgs a, int nchunks, float2* __restrict__ stats) {
   const int C = a.C1 + a.C2, cg = C / a.G;
   const GnShape sh = gn_shape(C);
-  const int qblocks = (a.HW + Q - 1) / Q;
-  const int row = blockIdx.x / qblocks, qb = blockIdx.x % qblocks;
-  const int t = threadIdx.x;
-  // 0. issue this thread's input vectors first: their latency overlaps the merge
-  const int p0 = qb * Q, np = min(Q, a.HW - p0);
-  const int64_t pix0 = (int64_t)row * a.HW + p0;
-  half8 xv[GN_APT];
-#pragma unroll
-  for (int j = 0; j < GN_APT; ++j) {
-    const int i = t + j * 256;
-    if (i < np * sh.nv) {
-      const int p = i / sh.nv, v = i - p * sh.nv;
-      xv[j] = load_vec(a, pix0 + p, v * 8);
-    }
-  }
-  // and the affine parameters of the channels this thread tabulates
-  float gam[GN_MAXC / 256], bet[GN_MAXC / 256];
-#pragma unroll
-  for (int j = 0; j < GN_MAXC / 256; ++j) {
-    const int c = t + j * 256;
-    gam[j] = c < C ? a.gamma[c] : 0.f;
-    bet[j] = c < C ? a.beta[c] : 0.f;
-  }
-  // 1. merge: TPG threads per group, chunks strided over them, then a fixed tree
+  const int row = blockIdx.x, t = threadIdx.x;
   const int TPG = 256 / a.G;  // G is a power of two in [4, 256]
   const int g = t / TPG, s = t % TPG;
   double n = 0.0, mean = 0.0, m2 = 0.0;
@@ -213,33 +188,46 @@ __global__ void __launch_bounds__(256) gn_apply_k(GnArgs a, int nchunks, int Q) 
     }
     n = n1; mean = mean1; m2 = m21;
   }
-  if (s == 0) {
-    gm[g] = (float)mean;
-    gr[g] = rsqrtf((float)(m2 / n) + a.eps);
-  }
-  __syncthreads();
+  if (s == 0) stats[row * a.G + g] = make_float2((float)mean, rsqrtf((float)(m2 / n) + a.eps));
+}
+
+// Thread t owns channel vector t % nv (its scale and shift in registers) for
+// GN_APX pixels, all requested before the first is used: HBM bounds it.  When
+// every workgroup merged the partials itself, the merge read as much as the
+// pixels: 16 x 4096 x 960 channels 88 us.
+constexpr int GN_APX = 8;
+__global__ void __launch_bounds__(256) gn_apply_k(GnArgs a, const float2* __restrict__ stats,
+                                                  int qblocks) {
+  const int C = a.C1 + a.C2, cg = C / a.G, nv = C / 8;
+  const int PP = nv <= 256 ? 256 / nv : 1;
+  const int row = blockIdx.x / qblocks, qb = blockIdx.x % qblocks;
+  const int t = threadIdx.x;
+  const int v = nv <= 256 ? t % nv : (int)blockIdx.y * 256 + t, phase = nv <= 256 ? t / nv : 0;
+  if (phase >= PP || v >= nv) return;
+  const int p0 = qb * PP * GN_APX + phase;
+  const int64_t pix0 = (int64_t)row * a.HW;
+  half8 x[GN_APX];
 #pragma unroll
-  for (int j = 0; j < GN_MAXC / 256; ++j) {
-    const int c = t + j * 256;
-    if (c < C) {
-      const int gg = c / cg;
-      const float k = gr[gg] * gam[j];
-      sc[c] = k;
-      sf[c] = bet[j] - gm[gg] * k;
-    }
+  for (int i = 0; i < GN_APX; ++i) {
+    const int p = p0 + i * PP;
+    x[i] = p < a.HW ? load_vec(a, pix0 + p, v * 8) : half8{};
   }
-  __syncthreads();
-  // 2. apply to pixels [qb * Q, qb * Q + Q) of this row
+  float k[8], f[8];
 #pragma unroll
-  for (int j = 0; j < GN_APT; ++j) {
-    const int i = t + j * 256;
-    if (i >= np * sh.nv) continue;
-    const int p = i / sh.nv, v = i - p * sh.nv;
+  for (int e = 0; e < 8; ++e) {
+    const int c = v * 8 + e;
+    const float2 st = stats[row * a.G + c / cg];
+    k[e] = st.y * a.gamma[c];
+    f[e] = a.beta[c] - st.x * k[e];
+  }
+#pragma unroll
+  for (int i = 0; i < GN_APX; ++i) {
+    const int p = p0 + i * PP;
+    if (p >= a.HW) break;
     half8 y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int c = v * 8 + e;
-      float r = fmaf((float)xv[j][e], sc[c], sf[c]);
+      float r = fmaf((float)x[i][e], k[e], f[e]);
       if (a.silu) r = silu(r);
       y[e] = (_Float16)r;
     }
@@ -306,26 +294,45 @@ __global__ void __launch_bounds__(256) layernorm_k(const _Float16* __restrict__ 
 // DDIM tables: abar_t accumulated in float64 and rounded to float32; for grid
 // step i: ts[i] = t_i = (N-1-i) T/N + 1, a_t[i] = abar(t_i), a_prev[i] =
 // abar(t_{i+1}) (abar_0 after the last step).  Requires T/N >= 2.
-__global__ void schedule_k(int T, int N, double b0, double b1, int32_t* ts, float* a_t,
-                           float* a_prev) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One workgroup: the factors in parallel, their running product by one thread
+// (left to right, as the table is defined), the table in parallel (one thread
+// doing all of it took 125 us, most of it in 1000 divisions).
+constexpr int SCHED_MAX_T = 1024;
+__global__ void __launch_bounds__(256) schedule_k(int T, int N, double b0, double b1, int32_t* ts,
+                                                  float* a_t, float* a_prev) {
+  __shared__ double f[SCHED_MAX_T];
   const int stride = T / N;
   const double r0 = sqrt(b0), r1 = sqrt(b1);
-  double acc = 1.0, abar0 = 1.0;
-  for (int t = 0; t < T; ++t) {
+  for (int t = threadIdx.x; t < T; t += 256) {
     const double rb = r0 + (r1 - r0) * (double)t / (double)(T - 1);
-    acc *= 1.0 - rb * rb;
-    if (t == 0) abar0 = acc;
-    if (t >= 1 && (t - 1) % stride == 0) {
-      const int i = N - 1 - (t - 1) / stride;
-      if (i >= 0 && i < N) {
-        ts[i] = t;
-        a_t[i] = (float)acc;
+    f[t] = 1.0 - rb * rb;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double acc = 1.0;
+    int t = 0;
+    for (; t + 8 <= T; t += 8) {
+      double x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = f[t + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        acc *= x[u];
+        f[t + u] = acc;
       }
     }
+    for (; t < T; ++t) {
+      acc *= f[t];
+      f[t] = acc;
+    }
   }
-  for (int i = 0; i + 1 < N; ++i) a_prev[i] = a_t[i + 1];
-  a_prev[N - 1] = (float)abar0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += 256) {
+    const int t = (N - 1 - i) * stride + 1;
+    ts[i] = t;
+    a_t[i] = (float)f[t];
+    a_prev[i] = (float)f[i + 1 < N ? t - stride : 0];
+  }
 }
 
 // Sinusoidal embedding [cos(t f_k), sin(t f_k)] of the timestep of each row.
@@ -810,19 +817,24 @@ hipError_t gn_launch(const GnArgs& a, int rows, hipStream_t s) {
       if (fits(nv)) return one((int)nv, S);
     }
     const int64_t nv = ceil_div(a.HW, P);  // rounds
-    if (fits(nv)) return one((int)nv, 1);
+    // 4-byte pieces of 20-byte group slices cost more than a second read of the
+    // activation in 16-byte vectors once there is enough of it (16 rows of 64 x
+    // 64 x 320: 86 us in one launch, 37 in three)
+    const bool narrow = vw == 2 && nv > 16 && (int64_t)rows * a.HW * C >= (int64_t(8) << 20);
+    if (fits(nv) && !narrow) return one((int)nv, 1);
   }
   const GnShape sh = gn_shape(C);
   const int nchunks = (int)ceil_div(a.HW, sh.P);
-  if (nchunks > a.part_chunks) return hipErrorInvalidValue;  // partial scratch too small
+  if (nchunks + 1 > a.part_chunks) return hipErrorInvalidValue;  // partial scratch too small
+  float2* stats = (float2*)(a.part + (int64_t)rows * nchunks * a.G * 2);
   if (sh.nown == 1)
     hipLaunchKernelGGL(gn_stats_k<1>, dim3(rows * nchunks), dim3(256), 0, s, a, nchunks);
   else
     hipLaunchKernelGGL(gn_stats_k<2>, dim3(rows * nchunks), dim3(256), 0, s, a, nchunks);
-  // at most GN_APT vectors per thread in the apply pass
-  const int Q = std::max(1, std::min(a.HW, GN_APT * 256 / sh.nv));
-  const int qblocks = (int)ceil_div(a.HW, Q);
-  hipLaunchKernelGGL(gn_apply_k, dim3(rows * qblocks), dim3(256), 0, s, a, nchunks, Q);
+  hipLaunchKernelGGL(gn_merge_k, dim3(rows), dim3(256), 0, s, a, nchunks, stats);
+  const int qblocks = (int)ceil_div(a.HW, sh.PP * GN_APX);
+  hipLaunchKernelGGL(gn_apply_k, dim3(rows * qblocks, (unsigned)ceil_div(sh.nv, 256)), dim3(256), 0,
+                     s, a, (const float2*)stats, qblocks);
   return hipGetLastError();
 }
 
@@ -835,7 +847,8 @@ hipError_t layernorm_launch(const _Float16* x, const float* g, const float* b, _
 
 hipError_t schedule_launch(int T, int N, double b0, double b1, int32_t* ts, float* a_t,
                            float* a_prev, hipStream_t s) {
-  hipLaunchKernelGGL(schedule_k, dim3(1), dim3(64), 0, s, T, N, b0, b1, ts, a_t, a_prev);
+  if (T > SCHED_MAX_T) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(schedule_k, dim3(1), dim3(256), 0, s, T, N, b0, b1, ts, a_t, a_prev);
   return hipGetLastError();
 }
 

@@ -414,7 +414,7 @@ void emit_gn(Builder& B, std::vector<Op>& ops, const Ten& x1, const Ten* x2, con
   const float* b = B.W32(n + ".b");
   const size_t o1 = x1.off, o2 = x2 ? x2->off : 0, oo = out.off;
   const size_t gp = B.P->gnpart;
-  const int part_chunks = (int)ceil_div(B.net_->cfg.H * B.net_->cfg.W, 8);
+  const int part_chunks = (int)ceil_div(B.net_->cfg.H * B.net_->cfg.W, 8) + 1;
   const int C1 = x1.C, C2 = x2 ? x2->C : 0, HW = x1.HW, G = cfg.gn_groups;
   const float eps = cfg.gn_eps;
   const bool has2 = x2 != nullptr;
@@ -738,7 +738,7 @@ std::unique_ptr<Plan> build_plan(nv_unet* net, int Rmax) {
   P->pooled = B.fixed((size_t)Bs * std::max(c.pooled_dim, 1) * 4);
   P->tproj = B.fixed((size_t)Rmax * net->temb_total * 4);
   int maxG = c.gn_groups;
-  P->gnpart = B.fixed((size_t)Rmax * ceil_div(HW0, 8) * maxG * 2 * 4);
+  P->gnpart = B.fixed((size_t)Rmax * (ceil_div(HW0, 8) + 1) * maxG * 2 * 4);
   P->splitk = B.fixed(SPLITK_BYTES);
   P->stepdev = B.fixed((size_t)2 * MAX_SAMPLES * 4);
   // per-call context K|V regions, one per transformer block
