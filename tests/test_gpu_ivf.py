@@ -64,3 +64,25 @@ def test_build_and_search_match_oracle(n, d, dtype, L, iters):
     ei, es, ek = P.nv_cache_lookup(q, cache, T, K)
     gi, gs, gk = index.search(q, L, T, K)
     assert torch.equal(gi, ei) and torch.equal(gs, es) and torch.equal(gk, ek)
+
+
+# widths around the 64-value slices and the 48-chunk loads, list counts around the 64-centroid
+# blocks, lists of several 256-row chunks, and equal rows (every one of them is summed canonically)
+@pytest.mark.parametrize("n,d,dtype,L,same", [(600, 2048, "bf16", 65, 5), (900, 72, "f32", 300, 3),
+                                              (1100, 520, "bf16", 2, 40), (513, 392, "f32", 1, 300)])
+def test_search_forms(n, d, dtype, L, same):
+    import paper_2312_04429_amd as P
+    print(f"ivf forms n={n} d={d} {dtype} L={L} same={same}", flush=True)
+    rng = np.random.default_rng(n + d)
+    X = synth.make_cache(n, d, 12, 0.15, n + d, dtype)
+    X[rng.choice(n, same, replace=False)] = X[n // 2]
+    init = rng.choice(n, L, replace=False)
+    index = P.NvIVF(_dev(X), init, 0)
+    c, _, perm, off = ivf.build(X, init, 0)
+    qn = _queries(X, 6, 7)
+    qn[0] = (synth.from_bf16_bits(X) if dtype == "bf16" else X)[n // 2]
+    for nprobe in sorted({1, min(17, L), min(256, L)}):
+        print(f"  search nprobe={nprobe}", flush=True)
+        got = index.search(torch.from_numpy(qn).cuda(), nprobe, T, K, probed=True)
+        for g, r in zip(got, ivf.search(qn, X, c, perm, off, nprobe, T, K)):
+            assert np.array_equal(g.cpu().numpy(), r)

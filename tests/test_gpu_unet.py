@@ -99,6 +99,36 @@ def test_eps_teacher_forced_strong_layernorm():
         net.close()
 
 
+@pytest.mark.parametrize("B", [6, 7])
+def test_eps_narrow_groups(B):
+    """Ten channels per GroupNorm group over 64 x 64: both sides of the size from which the
+    normalisation runs as statistics, merge and apply (8 Mi elements: 13 rows here), with gains
+    and shifts that differ from channel to channel."""
+    import paper_2312_04429_amd as P
+    cfg = synth.unet_config("tiny", H=64, W=64, ch=(160, 32), depth=(0, 0), mid_depth=0,
+                            gn_groups=16)
+    w = dict(synth.make_weights(cfg, 0))
+    rng = np.random.default_rng(5)
+    for k in w:
+        if ".gn" in k:
+            w[k] = (w[k] + rng.uniform(-0.5, 0.5, w[k].shape)).astype(np.float32)
+    net = P.NvUNet(cfg, w)
+    try:
+        ora = U.UNet(cfg, w)
+        x = synth.make_latents(B, 4, 64, 64, 7)
+        cond, unc = _ctx(cfg, B, 11), _ctx(cfg, B, 12)
+        print(f"narrow groups B={B}", flush=True)
+        eu, ec = net.nv_unet_eps(t(x), [9] * B, t(cond), t(unc), sched=SCHED(20))
+        ts = schedule.timesteps(20, 1000)[9]
+        for b in (0, B - 1):
+            du = np.abs(eu[b].cpu().numpy() - ora(x[b], ts, unc[b])).max()
+            dc = np.abs(ec[b].cpu().numpy() - ora(x[b], ts, cond[b])).max()
+            print(f"  b{b} maxabs u {du:.2e} c {dc:.2e}", flush=True)
+            assert du <= EPS_TOL and dc <= EPS_TOL
+    finally:
+        net.close()
+
+
 def _cached_state(ora, cfg, i, K, N):
     """State after K steps of a full oracle run for cached entry i (own prompt, own x_N)."""
     ctx = _ctx(cfg, 2, 1000 + i)
@@ -123,6 +153,26 @@ def test_denoise_single(tiny, K):
     err = rel_l2(got, ref)
     print(f"  rel-L2 {err:.2e}", flush=True)
     assert err <= X0_TOL
+
+
+@pytest.mark.parametrize("T,N,K", [(1024, 512, 510), (1000, 500, 0), (1023, 341, 340), (6, 3, 0),
+                                   (2, 1, 0)])
+def test_schedule_sizes(tiny, T, N, K):
+    """Step tables at the ends of their range and at lengths that are no multiple of eight: the
+    first or last few steps against the oracle's."""
+    cfg, _, net, ora = tiny
+    x = synth.make_latents(1, 4, cfg["H"], cfg["W"], 3)
+    cond, unc = _ctx(cfg, 1, 21), _ctx(cfg, 1, 22)
+    print(f"schedule T={T} N={N} K={K}", flush=True)
+    if N - K > 3:  # the table's first entry, through one evaluation
+        eu, _ = net.nv_unet_eps(t(x), [K], t(cond), t(unc), sched=(T, N) + SCHED(N)[2:])
+        ref = ora(x[0], schedule.timesteps(N, T)[K], unc[0])
+        assert np.abs(eu.cpu().numpy()[0] - ref).max() <= EPS_TOL
+        return
+    lat = t(x)
+    net.nv_denoise(lat, [K], t(cond), t(unc), guidance=7.5, sched=(T, N) + SCHED(N)[2:])
+    ref = ddim.denoise(U.make_eps_fn(ora, cond[0], unc[0]), x[0], K, N, dict(S, T=T), 7.5)
+    assert rel_l2(lat.cpu().numpy()[0], ref) <= X0_TOL
 
 
 def test_denoise_mixed_k_batch(tiny):
