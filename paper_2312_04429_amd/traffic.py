@@ -16,8 +16,8 @@ import json
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-FAMS = {"conv3x3_igemm": (("gemm_f16<1", "gemm_s<1"), ["gemm.hip", "gemm.h"]),
-        "linear_gemm": (("gemm_f16<0", "gemm_s<0"), ["gemm.hip", "gemm.h"]),
+FAMS = {"conv3x3_igemm": (("gemm_f16<1", "gemm_s<1", "gemm_w<1"), ["gemm.hip", "gemm.h"]),
+        "linear_gemm": (("gemm_f16<0", "gemm_s<0", "gemm_w<0"), ["gemm.hip", "gemm.h"]),
         "attention": (("attn_f16",), ["attention.hip"]),
         "cache_scan": (("lk_scan",), ["lookup.hip"])}
 CALIB_BYTES = float(1 << 30)
