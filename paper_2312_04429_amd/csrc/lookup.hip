@@ -13,9 +13,9 @@
 //      of the tile's rows, and once per tile an upper bound N_t on its row
 //      norms.  Nothing else leaves the scan.
 //   2. select: per query, L = max_t (M_tq - N_t E_q) is a lower bound on the
-//      best canonical score (lk_bound), and every row that can reach it lies
-//      in a tile with M_tq + N_t E_q >= L (listed by lk_mark).  Those tiles
-//      are read again (lk_select): a float64 dot in another summation order
+//      best canonical score, and every row that can reach it lies in a tile
+//      with M_tq + N_t E_q >= L (found by lk_finish; past its tile limit by
+//      lk_bound and lk_mark).  lk_finish reads those tiles again: a float64 dot in another summation order
 //      discards rows that provably cannot reach L; the rest are rescored with
 //      the canonical float64 left-to-right dot product; the maximum with the
 //      lowest index wins; its float32 rounding goes through the thresholds.
@@ -466,10 +466,16 @@ __global__ void __launch_bounds__(256, 2) lk_scan_bf16(const uint16_t* __restric
 // persistent workgroup per CU keeps HBM busy while it multiplies and an LDS
 // read of 1 KB feeds NBW multiplies instead of two (LDS reads bound the
 // kernel above at many queries: 256 queries over 4 M rows 2239 us against 1675,
-// 128 queries 1550 against 1238; at 64 the two are equal).  One wave per SIMD: the first PF fragments of the next block are
-// read ahead across the barrier.  Chunk c of row r sits at chunk c ^ (r & 15)
-// of its LDS row, as the queries do above.
-constexpr int MANY_M = 64;  // queries beyond which lk_scan_many is used
+// 128 queries 1550 against 1238; at 64 the two are equal).  One wave per SIMD:
+// the first PF fragments of the next block are read ahead across the barrier.
+// Chunk c of row r sits at chunk c ^ (r & 15) of its LDS row, as the queries do
+// above.
+// Queries beyond which it is used, by the padded row width: a ring of 16 narrow
+// rows a block holds few bytes in flight and pays a barrier per block, so up to
+// 384 wide it starts at 128 queries (200 k x 384: 64 queries 54 us above, 65
+// here 69; 256 here 88, 116 above with the finish it then had) and up to 128
+// wide never (200 k x 64: 64 queries 31 us above, 65 here 52).
+constexpr int many_from(int dp) { return dp <= 128 ? 1 << 30 : dp <= 384 ? 128 : 64; }
 constexpr int MANY_R = 6;  // row blocks in the ring (147 KB at d = 768)
 
 template <int NS, int NBW>
@@ -1228,8 +1234,8 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
   // bounds, tile list and rescan in one kernel for up to FIN_PER tiles a thread
   const int ft = m <= 256 ? 1024 : 256;
   const bool fused = T <= ft * FIN_PER;
-  // many queries stay in registers while the rows stream: past MANY_M queries
-  const bool many = rr && m > MANY_M;
+  // many queries stay in registers while the rows stream
+  const bool many = rr && m > many_from(dp);
   // the scan converts one or two queries itself (every workgroup does: 8 queries
   // over 1 M rows 260 us against 243 with lk_prep's copy)
   const bool convert = rr && !many && m <= 2;
@@ -1257,7 +1263,7 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
   case ns:          \
     if (nbw == 4)   \
       NV_MANY1(ns, 4) else NV_MANY1(ns, 2) break;
-        NV_MANY(4) NV_MANY(8) NV_MANY(12) NV_MANY(16) NV_MANY(20) NV_MANY(24)
+        NV_MANY(8) NV_MANY(12) NV_MANY(16) NV_MANY(20) NV_MANY(24)
 #undef NV_MANY
 #undef NV_MANY1
       }

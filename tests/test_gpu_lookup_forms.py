@@ -24,7 +24,8 @@ def _case(n, d, m, seed):
 
 @pytest.mark.parametrize("n,d,m,dtype", [
     (5000, 64, 65, "bf16"), (129, 96, 100, "bf16"), (40_001, 768, 129, "bf16"), (15, 768, 128, "bf16"),
-    (1500, 328, 256, "bf16"), (777, 512, 300, "bf16"), (3000, 640, 1, "bf16"), (3001, 768, 2, "bf16"),
+    (1500, 328, 256, "bf16"), (2000, 128, 260, "bf16"), (2000, 136, 129, "bf16"),
+    (2000, 384, 128, "bf16"), (2000, 392, 65, "bf16"), (777, 512, 300, "bf16"), (3000, 640, 1, "bf16"), (3001, 768, 2, "bf16"),
     (3001, 768, 3, "bf16"), (5000, 1000, 33, "f32"), (257, 40, 17, "f32"), (1023, 768, 16, "f32"),
     (600, 2048, 40, "f32"), (3000, 768, 300, "f32")])
 def test_lookup_forms(n, d, m, dtype):
