@@ -427,6 +427,10 @@ __global__ void __launch_bounds__(256) top_lists_k(const double* __restrict__ cs
 // then the additions in order.  The result is the best (score, lowest row) of
 // the block, as if every row had been summed (one query, 32 lists of about a
 // thousand rows: 54 us with a canonical sum per row against 29).
+// A score that is not a number is neither above nor below another, so with one
+// among the rows the result depends on the order of the comparisons: every row of
+// such a block is summed and the scores are compared in the fixed tree of
+// probe_final_k over list positions.
 constexpr int PS_T = 512;
 
 __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q, int d,
@@ -444,6 +448,7 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   __shared__ double fast[256], tols[256];
   __shared__ double red[NWV], rs[NWV];
   __shared__ int64_t ri[NWV];
+  __shared__ int64_t ids[256];
   __shared__ int surv[256];
   __shared__ int n_surv;
   const int jp = blockIdx.x, ch = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -461,6 +466,7 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   const char* rows = (const char*)lrows + p0 * d * (bf ? 2 : 4);
   load_query(qd, q + (int64_t)j * d, d);
   if (t == 0) n_surv = 0;
+  if (t < 256) ids[t] = t < nrows ? perm[p0 + t] : -1;
   __syncthreads();
   double qq = 0.0;
   for (int k = t; k < d; k += PS_T) qq = fma(qd[k], qd[k], qq);
@@ -531,8 +537,11 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   if (lane == 0) rs[wave] = lo;
   __syncthreads();
   for (int w = 0; w < NWV; ++w) lo = fmax(lo, rs[w]);
-  // a dot that is not a number is summed canonically too
-  if (t < nrows && !(fast[t] + (scale * tols[t] + 0x1p-1000) < lo)) surv[atomicAdd(&n_surv, 1)] = t;
+  // the products decide whether a sum is a number, whatever its order; a bound that is
+  // not a number rules nothing out
+  const bool any_nan = __syncthreads_or(t < nrows && isnan(fast[t])) != 0;
+  if (t < nrows && (any_nan || !(fast[t] + (scale * tols[t] + 0x1p-1000) < lo)))
+    surv[atomicAdd(&n_surv, 1)] = t;
   __syncthreads();
   double bs = -INFINITY;
   int64_t bi = -1;
@@ -560,14 +569,31 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
           s = __dadd_rn(s, y.y);
         }
       __builtin_amdgcn_wave_barrier();
-      const int64_t row = perm[p0 + r];
-      if (bi < 0 || better_pair(s, row, bs, bi)) {
+      const int64_t row = ids[r];
+      if (any_nan) {
+        if (lane == 0) fast[r] = s;
+      } else if (bi < 0 || better_pair(s, row, bs, bi)) {
         bs = s;
         bi = row;
       }
     }
   }
   __syncthreads();  // rs held the bounds
+  if (any_nan) {
+    for (int w = 128; w > 0; w >>= 1) {
+      if (t < w && ids[t + w] >= 0 &&
+          (ids[t] < 0 || better_pair(fast[t + w], ids[t + w], fast[t], ids[t]))) {
+        fast[t] = fast[t + w];
+        ids[t] = ids[t + w];
+      }
+      __syncthreads();
+    }
+    if (t == 0) {
+      ps[(int64_t)jp * chunks + ch] = fast[0];
+      pi[(int64_t)jp * chunks + ch] = ids[0];
+    }
+    return;
+  }
   if (lane == 0) {
     rs[wave] = bs;
     ri[wave] = bi;

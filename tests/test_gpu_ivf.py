@@ -86,3 +86,53 @@ def test_search_forms(n, d, dtype, L, same):
         got = index.search(torch.from_numpy(qn).cuda(), nprobe, T, K, probed=True)
         for g, r in zip(got, ivf.search(qn, X, c, perm, off, nprobe, T, K)):
             assert np.array_equal(g.cpu().numpy(), r)
+
+
+def _tree(scores, ids):
+    """(score, id) that the fixed comparison tree over 256 slots leaves in slot 0."""
+    s, i = list(scores) + [-np.inf] * (256 - len(scores)), list(ids) + [-1] * (256 - len(ids))
+    w = 128
+    while w:
+        for t in range(w):
+            a, b = t + w, t
+            if i[a] >= 0 and (i[b] < 0 or s[a] > s[b] or (s[a] == s[b] and i[a] < i[b])):
+                s[b], i[b] = s[a], i[a]
+        w //= 2
+    return s[0], i[0]
+
+
+@pytest.mark.parametrize("n,d,dtype,L", [(900, 64, "f32", 2), (700, 72, "bf16", 3)])
+def test_rows_that_are_not_finite(n, d, dtype, L):
+    """Scores that are not numbers are ordered by the comparison tree alone: with NaN and infinite
+    rows in the lists every call gives the answer of the tree over list positions, then over the
+    probes' chunks."""
+    import paper_2312_04429_amd as P
+    print(f"ivf not finite n={n} d={d} {dtype} L={L}", flush=True)
+    X = synth.make_cache(n, d, 12, 0.15, n + d, dtype)
+    index = P.NvIVF(_dev(X), np.arange(L) * (n // L), 0)
+    rng = np.random.default_rng(d)
+    at = torch.from_numpy(rng.choice(n, 60, replace=False)).cuda()
+    flat = index.rows.view(torch.bfloat16) if dtype == "bf16" else index.rows
+    for part, v in zip(at.chunk(4), (np.nan, np.inf, -np.inf, 3e38)):
+        flat[part, int(rng.integers(d))] = float(v)
+    rows = flat.double().cpu().numpy()
+    perm, off = index.perm.cpu().numpy(), index.offsets.cpu().numpy()
+    q = _queries(X, 8, 3)
+    q[5] = np.nan
+    got = [[a.cpu().numpy() for a in index.search(torch.from_numpy(q).cuda(), L, T, K, probed=True)]
+           for _ in range(12)]
+    with np.errstate(invalid="ignore", over="ignore"):
+        for j in range(len(q)):
+            s = np.zeros(n)
+            for k in range(d):
+                s = s + float(q[j, k]) * rows[:, k]
+            parts = []
+            for l in got[0][3][j]:
+                for c in range(off[l], off[l] + 256 * max(1, -(-index.max_list // 256)), 256):
+                    e = min(c + 256, off[l + 1])
+                    parts.append(_tree(s[c:e], perm[c:e]) if c < e else (-np.inf, -1))
+            assert len(parts) <= 256
+            best, row = _tree(*zip(*parts))
+            for r in got:
+                assert r[0][j] == row
+                assert np.array_equal(r[1][j], np.float32(best), equal_nan=True)
