@@ -24,6 +24,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "lookup_rule.h"
 #include "trace.h"
 
 namespace nv {
@@ -470,12 +471,7 @@ __global__ void __launch_bounds__(256, 2) lk_scan_bf16(const uint16_t* __restric
 // the first PF fragments of the next block are read ahead across the barrier.
 // Chunk c of row r sits at chunk c ^ (r & 15) of its LDS row, as the queries do
 // above.
-// Queries beyond which it is used, by the padded row width: a ring of 16 narrow
-// rows a block holds few bytes in flight and pays a barrier per block, so up to
-// 384 wide it starts at 128 queries (200 k x 384: 64 queries 54 us above, 65
-// here 69; 256 here 88, 116 above with the finish it then had) and up to 128
-// wide never (200 k x 64: 64 queries 31 us above, 65 here 52).
-constexpr int many_from(int dp) { return dp <= 128 ? 1 << 30 : dp <= 384 ? 128 : 64; }
+// Where it is used: resident_query_blocks (lookup_rule.h).
 constexpr int MANY_R = 6;  // row blocks in the ring (147 KB at d = 768)
 
 template <int NS, int NBW>
@@ -492,7 +488,6 @@ __global__ void __launch_bounds__(256, 1) lk_scan_many(const uint16_t* __restric
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, kc = lane >> 4;
   const int q0 = blockIdx.y * 64 * NBW + wave * 16 * NBW;  // first query of this wave
-  const int64_t nblk = (n + 15) / 16;
   // tiles of 8 row blocks, dealt round-robin to the workgroups
   const int T = ws.T, G = gridDim.x;
   const int my_tiles = ((int)blockIdx.x < T) ? (T - 1 - (int)blockIdx.x) / G + 1 : 0;
@@ -1234,8 +1229,9 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
   // bounds, tile list and rescan in one kernel for up to FIN_PER tiles a thread
   const int ft = m <= 256 ? 1024 : 256;
   const bool fused = T <= ft * FIN_PER;
-  // many queries stay in registers while the rows stream
-  const bool many = rr && m > many_from(dp);
+  // query blocks a wave holds while the rows stream (0: rows are held)
+  const int nbw = rr ? resident_query_blocks(T, dp, m) : 0;
+  const bool many = nbw > 0;
   // the scan converts one or two queries itself (every workgroup does: 8 queries
   // over 1 M rows 260 us against 243 with lk_prep's copy)
   const bool convert = rr && !many && m <= 2;
@@ -1249,7 +1245,6 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
       const size_t lds = (size_t)MANY_R * 16 * dp * 2 + 8 * 4;
       const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d);
       const uint16_t* cb = (const uint16_t*)cache;
-      const int nbw = m > 128 ? 4 : 2;
       const dim3 grid((unsigned)std::min(T, 256), (unsigned)ceil_div(m, 64 * nbw));
 #define NV_MANY1(ns, w)                                                                         \
   {                                                                                             \
@@ -1264,6 +1259,9 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
     if (nbw == 4)   \
       NV_MANY1(ns, 4) else NV_MANY1(ns, 2) break;
         NV_MANY(8) NV_MANY(12) NV_MANY(16) NV_MANY(20) NV_MANY(24)
+        default:
+          set_error("no query-resident scan of this width");
+          return NV_ERR_UNSUPPORTED;
 #undef NV_MANY
 #undef NV_MANY1
       }
