@@ -297,8 +297,10 @@ __device__ inline void epilogue_tile(const GemmArgs& g, int64_t mb, int nb, int 
 // Straight from the accumulators a wave's store touches 16 rows in 32-byte
 // pieces: the last tiles of a 256 x 256 grid then take 27 us to drain.
 // GEGLU quads are combined in registers (as in epilogue_tile) and staged at
-// half the columns.  With KG > 1 wave group kg holds its share of K's sums:
-// the groups add theirs to the staged rows in group order.  The arithmetic and
+// half the columns, where a wave holds all of K and whole 32-column groups
+// (KG == 1, FN even); the launcher gives the other forms none.  With KG > 1 wave
+// group kg holds its share of K's sums: the groups add theirs to the staged rows in
+// group order.  The arithmetic and
 // its order are those of store_out4 / store_geglu4; the transposed columns (vt)
 // go out as 8 consecutive tokens of one channel.
 // st: LDSB bytes of LDS that no wave reads or loads into any more.  With LN,
@@ -384,41 +386,6 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& g, float* st, int6
     __syncthreads();
     auto row_of = [&](int r) { return (r / (16 * IB)) * WM + i0 * 16 + r % (16 * IB); };
     auto live = [&](int r) { return i0 + (r % (16 * IB)) / 16 < FM && row_of(r) < M; };
-    if (g.geglu) {  // staged columns in groups of (16 "a", 16 gates); 8 outputs per thread
-      constexpr int CH = BN / 16;
-      for (int e = tid; e < ROWS * CH; e += NT) {
-        const int r = e / CH, c = e % CH;
-        const int na = (c >> 1) * 32 + (c & 1) * 8;  // first "a" column in the tile
-        if (!live(r) || n0 + na + 16 >= g.N) continue;
-        const float4* p = (const float4*)&st[r * SR + na];
-        const float4* b = (const float4*)(g.bias + n0 + na);
-        half8 h;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          float4 av = p[q], gv = p[4 + q];
-          if (LN) {
-            const float2 s = ln[row_of(r)];
-            const float4 ca = *(const float4*)(g.ln_c1 + n0 + na + 4 * q);
-            const float4 cg = *(const float4*)(g.ln_c1 + n0 + na + 16 + 4 * q);
-            av.x = s.y * (av.x - s.x * ca.x); av.y = s.y * (av.y - s.x * ca.y);
-            av.z = s.y * (av.z - s.x * ca.z); av.w = s.y * (av.w - s.x * ca.w);
-            gv.x = s.y * (gv.x - s.x * cg.x); gv.y = s.y * (gv.y - s.x * cg.y);
-            gv.z = s.y * (gv.z - s.x * cg.z); gv.w = s.y * (gv.w - s.x * cg.w);
-          }
-          if (g.bias) {
-            const float4 ba = b[q], bg = b[4 + q];
-            av.x += ba.x; av.y += ba.y; av.z += ba.z; av.w += ba.w;
-            gv.x += bg.x; gv.y += bg.y; gv.z += bg.z; gv.w += bg.w;
-          }
-          h[4 * q] = (_Float16)(av.x * gelu_erf(gv.x));
-          h[4 * q + 1] = (_Float16)(av.y * gelu_erf(gv.y));
-          h[4 * q + 2] = (_Float16)(av.z * gelu_erf(gv.z));
-          h[4 * q + 3] = (_Float16)(av.w * gelu_erf(gv.w));
-        }
-        *(half8*)((_Float16*)g.out + (m0 + row_of(r)) * g.ldo + (n0 >> 1) + c * 8) = h;
-      }
-      continue;
-    }
     constexpr int CH = BN / 8;
     for (int e = tid; e < ROWS * CH; e += NT) {
       const int r = e / CH, c = e % CH;
@@ -1626,8 +1593,9 @@ hipError_t launch_s(const GemmArgs& g, int splits, hipStream_t s) {
 template <int MODE, int BM, int BN, int WGM, int WGN, int KH, int KT, int STAGES, bool LN>
 hipError_t launch_w_t(const GemmArgs& g, hipStream_t s) {
   constexpr int NW = KT * KH * WGM * WGN;
-  // GEGLU's 32-column groups may not straddle tiles
-  if (!g.rows_ok || g.K % 64 != 0 || (g.geglu && BN % 32 != 0)) return hipErrorInvalidValue;
+  if (!g.rows_ok || g.K % 64 != 0) return hipErrorInvalidValue;
+  // epilogue_rows pairs GEGLU's quads in the registers of one wave
+  if (g.geglu && (KH * KT != 1 || (BN / WGN / 16) % 2 != 0)) return hipErrorInvalidValue;
   if (g.bytes1 >= 0x80000000u || g.bytes2 >= 0x80000000u ||
       (int64_t)g.N * g.ldw * 2 >= 0x80000000ll)
     return hipErrorInvalidValue;  // descriptors address less than 2 GiB (gemm_launch chunks)
