@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gelu.h"
 #include "gemm.h"
 #include "trace.h"
 
@@ -54,24 +55,12 @@ __device__ inline uint4 bload(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// x Phi(x).  With a = |x| and t = 1 / (1 + 0.23 a), Phi(-a) = exp(-a^2 / 2) t P(t),
-// P a degree-7 polynomial fitted (weighted least squares over [0, 8]) to 3.9e-8
-// relative error.  Against float64 over N(0, 2^2) inputs: 2.7e-8 in the 2-norm
-// (erff: 3.5e-8, which cancels in 1 + erf for negative x), float16 results off
-// by a rounding for 0.014 % of inputs (erff: 1.5 %).  erff's two branches cost
-// a 16384 x 5120 x 640 GEGLU product about a third of its time.
-__device__ inline float gelu_erf(float x) {
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.23f, fabsf(x), 1.0f));
-  float p = -0.07659625917836188f;
-  p = fmaf(p, t, 0.2807779878031606f);
-  p = fmaf(p, t, -0.2568776671746554f);
-  p = fmaf(p, t, 0.27530439510780197f);
-  p = fmaf(p, t, -0.013266265758262716f);
-  p = fmaf(p, t, 0.11030993488071447f);
-  p = fmaf(p, t, 0.08838350014029378f);
-  p = fmaf(p, t, 0.09196435534591353f);
-  const float h = p * t * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);
-  return x * (x >= 0.0f ? 1.0f - h : h);
+struct DeviceMath {
+  static __device__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+  static __device__ float exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+};
+__device__ __forceinline__ void gelu4(const float (&x)[4], float (&y)[4]) {
+  gelu_quad<DeviceMath>(x, y);
 }
 __device__ inline float silu(float x) { return x / (1.0f + __expf(-x)); }
 
@@ -135,16 +124,19 @@ __device__ inline void store_out4(const GemmArgs& g, int64_t m, int n, float (&v
 // columns later); output columns oc..oc+3 with oc = (na / 32) * 16 + na % 32.
 __device__ inline void store_geglu4(const GemmArgs& g, int64_t m, int na, const float (&a)[4],
                                     const float (&gt)[4], bool vec) {
-  float y[4];
+  float av[4], gv[4], y[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    float av = a[r], gv = gt[r];
+    av[r] = a[r];
+    gv[r] = gt[r];
     if (g.bias) {
-      av += g.bias[na + r];
-      gv += g.bias[na + 16 + r];
+      av[r] += g.bias[na + r];
+      gv[r] += g.bias[na + 16 + r];
     }
-    y[r] = av * gelu_erf(gv);
   }
+  gelu4(gv, y);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) y[r] *= av[r];
   const int oc = (na >> 5) * 16 + (na & 15);
   _Float16* o = (_Float16*)g.out + m * g.ldo + oc;
   if (vec) {
@@ -193,16 +185,19 @@ __device__ inline void epilogue_tile(const GemmArgs& g, int64_t mb, int nb, int 
       for (int jj = 0; jj < FN / 2; ++jj) {
         const int na = nb + 2 * jj * 16 + kc * 4;
         if (na + 16 >= g.N) continue;
-        float y[4];
+        float av[4], gv[4], y[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          float av = acc[i][2 * jj][r], gv = acc[i][2 * jj + 1][r];
+          av[r] = acc[i][2 * jj][r];
+          gv[r] = acc[i][2 * jj + 1][r];
           if (g.bias) {
-            av += bq[2 * jj][r];
-            gv += bq[2 * jj + 1][r];
+            av[r] += bq[2 * jj][r];
+            gv[r] += bq[2 * jj + 1][r];
           }
-          y[r] = av * gelu_erf(gv);
         }
+        gelu4(gv, y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[r] *= av[r];
         const int oc = (na >> 5) * 16 + (na & 15);
         _Float16* o = (_Float16*)g.out + m * g.ldo + oc;
         if (vec) {
@@ -351,11 +346,14 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& g, float* st, int6
             a = s.y * (a - s.x * ca[jj]);
             t = s.y * (t - s.x * cg[jj]);
           }
+          const float gv[4] = {t[0] + bg[jj].x, t[1] + bg[jj].y, t[2] + bg[jj].z, t[3] + bg[jj].w};
+          float y[4];
+          gelu4(gv, y);
           half4 h;
-          h[0] = (_Float16)((a[0] + ba[jj].x) * gelu_erf(t[0] + bg[jj].x));
-          h[1] = (_Float16)((a[1] + ba[jj].y) * gelu_erf(t[1] + bg[jj].y));
-          h[2] = (_Float16)((a[2] + ba[jj].z) * gelu_erf(t[2] + bg[jj].z));
-          h[3] = (_Float16)((a[3] + ba[jj].w) * gelu_erf(t[3] + bg[jj].w));
+          h[0] = (_Float16)((a[0] + ba[jj].x) * y[0]);
+          h[1] = (_Float16)((a[1] + ba[jj].y) * y[1]);
+          h[2] = (_Float16)((a[2] + ba[jj].z) * y[2]);
+          h[3] = (_Float16)((a[3] + ba[jj].w) * y[3]);
           *(half4*)&sh[(wm * WM + i * 16 + li) * SH + wn * (WN / 2) + jj * 16 + kc * 4] = h;
         }
       __syncthreads();
