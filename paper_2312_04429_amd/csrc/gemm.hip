@@ -29,6 +29,7 @@
 #include "common.h"
 #include "gelu.h"
 #include "gemm.h"
+#include "gemm_rule.h"
 #include "trace.h"
 
 namespace nv {
@@ -1642,161 +1643,35 @@ hipError_t launch(const GemmArgs& g, int splits, hipStream_t s) {
               : launch_t<MODE, BM, BN, false>(g, splits, s);
 }
 
-// Forms of the wide kernel with their measured cost in us: a launch costs
-// about 5, a round of tiles f + s per 64-deep k tile (f1, s1 with one
-// workgroup per CU; f2, s2 with two where two fit, both finishing).  The
-// constants are linear fits to graph-free timings on the UNet's shapes (6 to
-// 180 k tiles, 80 to 2560 tiles), which they match within about 8 %:
-// 4096 x 1280 x 5120 56 us (128 x 128 tiles of gemm_s: 77), 4096 x 3840 x 1280
-// 45 (54), 65536 x 960 x 320 73 (82), 2048 x 640 x 2560 16.2 (22.5), 1024 x
-// 1280 x 5120 26 (35), 3x3 convolutions over 16 x 32 x 32 640 -> 640 105
-// (145), 16 x 16 x 16 1280 -> 1280 117 (150), 2 x 32 x 32 640 -> 640 28 (34.5).
-struct WideForm {
-  int bm, bn, per_cu;
-  float f1, s1, f2, s2;
-};
-constexpr WideForm WIDE[] = {
-    {256, 256, 1, 10.0f, 1.40f, 0.f, 0.f},   // 0: 8 waves of 128 x 64
-    {256, 160, 1, 8.5f, 1.02f, 0.f, 0.f},    // 1: 8 waves of 64 x 80
-    {128, 160, 2, 5.0f, 0.65f, 7.0f, 1.12f}, // 2: 8 waves of 32 x 80
-    {128, 160, 1, 6.0f, 0.58f, 0.f, 0.f},    // 3: 2 k halves x 4 waves of 64 x 80
-    {128, 128, 2, 1.4f, 0.59f, 5.2f, 0.94f}, // 4: 8 waves of 64 x 32
-    {64, 160, 1, 2.0f, 0.385f, 0.f, 0.f},    // 5: 2 k halves x 4 waves of 32 x 80
-    {128, 80, 2, 1.7f, 0.37f, 4.0f, 0.68f},  // 6: 2 k halves x 4 waves of 32 x 80
-    {64, 128, 2, 0.3f, 0.29f, 4.2f, 0.58f},  // 7: 2 k halves x 4 waves of 32 x 64
-    {64, 80, 1, 1.0f, 0.25f, 0.f, 0.f},      // 8: 2 k halves x 2 teams x 2 waves of 32 x 80
-    {64, 64, 2, 0.2f, 0.19f, 1.6f, 0.375f},  // 9: 2 k halves x 4 waves of 32 x 32
-};
-constexpr int NCU = 256;
-
-float wide_cost(const WideForm& w, const GemmArgs& g) {
-  const int64_t tiles = ceil_div(g.M, w.bm) * ceil_div(g.N, w.bn);
-  const float n = (float)(g.K / 64), one = w.f1 + n * w.s1;
-  if (w.per_cu == 1) return 5.0f + (float)ceil_div(tiles, NCU) * one;
-  const int64_t rem = tiles % (2 * NCU);
-  const float two = w.f2 + n * w.s2;
-  return 5.0f + (float)(tiles / (2 * NCU)) * two + (rem == 0 ? 0.f : rem <= NCU ? one : two);
-}
-
-// The cheapest form, or -1 where the kernels below are the better choice: the
-// row-staged epilogue does not apply, or K is long enough over a grid small
-// enough that split K pays (about 16 us + 800 TFLOP/s with its reduction, inside
-// the network: the 2 x 16 x 16 1280 -> 1280 convolution 32 us against 39 to 46;
-// 512 x 1280 x 5120 26.5 us split, 20 unsplit).  GEGLU combines its quads in
-// registers (forms 0 and 4; from staged rows 512 x 10240 x 1280 takes 35 us).
-int wide_form(const GemmArgs& g) {
-  if (!g.rows_ok) return -1;
-  int best = -1;
-  float cost = 1e30f;
-  for (int i = 0; i < (int)(sizeof(WIDE) / sizeof(WIDE[0])); ++i) {
-    if (g.geglu && i != 0 && i != 4) continue;
-    const float c = wide_cost(WIDE[i], g);
-    if (c < cost) {
-      cost = c;
-      best = i;
-    }
-  }
-  const bool can_split = g.partial && !g.ln_c1 && !g.geglu && g.K / 64 >= 20 &&
-                         (size_t)2 * g.M * g.N * 4 <= g.partial_bytes;
-  if (can_split && 16.0f + 2.0f * (float)g.M * (float)g.N * (float)g.K / 800e6f < cost) return -1;
-  return best;
-}
-
 template <int MODE>
 hipError_t dispatch_wide(const GemmArgs& g, int form, hipStream_t s) {
-  switch (form) {
+  switch (form) {  // in the order of WIDE
     case 0: return launch_w<MODE, 256, 256, 2, 4, 1, 1, 2>(g, s);
     case 1: return launch_w<MODE, 256, 160, 4, 2, 1, 1, 2>(g, s);
     case 2: return launch_w<MODE, 128, 160, 4, 2, 1, 1, 2>(g, s);
     case 3: return launch_w<MODE, 128, 160, 2, 2, 2, 1, 3>(g, s);
     case 4: return launch_w<MODE, 128, 128, 2, 4, 1, 1, 2>(g, s);
-    case 5: return launch_w<MODE, 64, 160, 2, 2, 2, 1, 4>(g, s);
-    case 6: return launch_w<MODE, 128, 80, 4, 1, 2, 1, 3>(g, s);
-    case 7: return launch_w<MODE, 64, 128, 2, 2, 2, 1, 3>(g, s);
-    case 8: return launch_w<MODE, 64, 80, 2, 1, 2, 2, 3>(g, s);
-    case 9: return launch_w<MODE, 64, 64, 2, 2, 2, 1, 4>(g, s);
+    case 5: return launch_w<MODE, 128, 80, 4, 1, 2, 1, 3>(g, s);
+    case 6: return launch_w<MODE, 64, 128, 2, 2, 2, 1, 3>(g, s);
+    case 7: return launch_w<MODE, 64, 80, 2, 1, 2, 2, 3>(g, s);
+    case 8: return launch_w<MODE, 64, 64, 2, 2, 2, 1, 4>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-// Tile choice for the streamed kernel (GPU time measured on the UNet's
-// shapes).  A workgroup here is bound by the latency of its k-tile loads
-// (about 0.4 us per tile), so small tiles and many resident workgroups win:
-// 64 x 64 tiles with a three-deep ring by default (inside the network the
-// weights arrive cold from HBM, where the third buffer pays); K is split when it is long
-// (>= 40 tiles) or the grid is tiny, keeping >= MIN_KT tiles per split and
-// about 700 workgroups at most.  Large grids take 128 x 128 tiles for very
-// wide (N >= 2560) or very deep (K >= 8192) products and the 320-channel
-// convolutions, 64 x 128 otherwise; a long K over a mid-sized grid, and a
-// deep convolution over 32 to 128 such tiles, take split 128 x 128.
+// Streamed products: the form is stream_plan's choice (gemm_rule.h).
 template <int MODE>
 hipError_t dispatch_streamed(const GemmArgs& g, hipStream_t s) {
-  const int form = wide_form(g);
-  if (form >= 0) return dispatch_wide<MODE>(g, form, s);
-  constexpr int MIN_KT = 10;
-  const int nk = g.K / 64;
-  const int64_t t128 = ceil_div(g.M, 128) * ceil_div(g.N, 128);
-  const int64_t t64 = ceil_div(g.M, 64) * ceil_div(g.N, 64);
-  auto split_to = [&](int64_t tiles, int64_t target) {
-    int sp = 1;
-    if (!g.partial || (g.N & 3) != 0) return 1;
-    while (tiles * (sp + 1) <= target && nk / (sp + 1) >= MIN_KT &&
-           (size_t)(sp + 1) * g.M * g.N * 4 <= g.partial_bytes)
-      ++sp;
-    return sp;
-  };
-  if (t64 >= 1024) {
-    // large grids: 128 x 128 for very wide products with at least ~6 such tiles
-    // per CU, very deep products and the narrow 320-channel convolutions, 64 x 128
-    // otherwise (graph-timed on the batched SD-1.5 and SDXL shapes; the batch-1
-    // feed-forward products, 320 to 1280 tiles of 128 x 128, run 8 to 22 % faster
-    // at 64 x 128)
-    // (and, measured on the SDXL level-2 and batch-8 shapes, 128 x 128 for at least
-    // 4096 rows when wide with K >= 1280 or deep with N >= 1280: q|k|v 4096x3840x1280
-    // 76.6 -> 55.6 us, 4096x1280x5120 85.1 -> 74.0 us; the 640-channel
-    // convolutions and 16384-row products below 2560 columns stay at 64 x 128)
-    // 128 x 128 tiles run eight waves (2 x 4 wave tiles of 64 x 32): half the
-    // accumulators per wave, two waves per SIMD from one workgroup (graph-timed:
-    // 16384 x 5120 x 640 182 -> 168 us, 65536 x 2560 x 320 258 -> 226 us, the
-    // 320-channel convolution over 65536 pixels 161 -> 148 us); dense products
-    // over at least 8192 rows and 960 columns take them too (8192 x 960 x 320
-    // 17.0 -> 14.3 us, 8192 x 2560 x 320 32.7 -> 30.2 us against 64 x 128).
-    // 64 x 128 tiles run eight waves as well (2 x 4 wave tiles of 32 x 32; guided
-    // steps measured together: b1 5.257 -> 5.232 ms, b8 2.982 -> 2.965 ms, SDXL 22.27 ->
-    // 22.09 ms, with the wide products below)
-    const bool big = (g.N >= 2560 && t128 >= 1536) || g.K >= 8192 || g.N <= 320 ||
-                     (g.M >= 4096 && g.N >= 2560 && g.K >= 1280) ||
-                     (g.M >= 4096 && g.N >= 1280 && g.K >= 4096) ||
-                     (MODE == 0 && g.M >= 8192 && g.N >= 960);
-    return big ? launch_s<MODE, 128, 128, GEMM_S128, 1, 8>(g, 1, s)
-               : launch_s<MODE, 64, 128, 2, 1, 8>(g, 1, s);
-  }
-  if (t128 >= 128 && nk >= 128)
-    return launch_s<MODE, 128, 128, GEMM_S128>(g, split_to(t128, 512), s);
-  // deep convolutions over mid-sized grids (batch 1 at 32 x 32 and 16 x 16):
-  // 128 x 128 tiles halve the bytes per flop, split K refills the chip
-  // (graph-timed 47 against 64 us at 32 x 32 with 1280 input channels); eight
-  // waves (b1 guided step 5.296 -> 5.279 ms against four)
-  if (MODE == 1 && t128 >= 32 && t128 <= 128 && nk >= 80)
-    return launch_s<MODE, 128, 128, GEMM_S128, 1, 8>(g, split_to(t128, 700), s);
-  // split K past 40 k tiles, or below about 100 tiles (graph-timed alone:
-  // 2048 x 640 x 2560 22.2 -> 19.6 us and 512 x 1280 x 2560 17.9 -> 15.9 us
-  // unsplit, 128 x 3840 x 1280 10.8 -> 9.5 us)
-  const bool split = nk > 40 || t64 < 100;
-  // wide products just under the large-grid bound (batch-1 level-1 q|k|v,
-  // 2048 x 1920 x 640: 15.2 -> 12.2 us graph-timed) take 64 x 128 tiles
-  if (!split && t64 >= 768 && g.N >= 1920) return launch_s<MODE, 64, 128, 2, 1, 8>(g, 1, s);
-  // convolutions aim at fewer workgroups in total: fewer float32 partials to
-  // write and sum (b1 guided step: the batch-1 8 x 8 convolutions at 12 splits
-  // instead of 17, 5.365 -> 5.318 ms; 15 splits 5.360, 10 splits 5.346)
-  const int spl = split ? split_to(t64, MODE == 1 ? 480 : 700) : 1;
-  // up to about two workgroups per CU: eight waves in 2 x 4 wave tiles of
-  // 32 x 16 (b1 guided step 5.208 -> 5.131 ms; swept: 5.255 -> 5.198, 5.213
-  // with every 64 x 64 grid, 5.225 up to one workgroup per CU) and a four-tile
-  // ring, 64 KB, two workgroups per CU (5.131 -> 5.117 ms; two tiles 5.478).
-  // The GEGLU epilogue pairs 16-column quads inside a wave and keeps four.
-  if (!g.geglu && t64 * spl <= 512) return launch_s<MODE, 64, 64, 4, 1, 8>(g, spl, s);
-  return launch_s<MODE, 64, 64, GEMM_S64>(g, spl, s);
+  const StreamPlan p =
+      stream_plan({g.M, g.N, g.K, MODE == 1, g.geglu != 0, g.ln_c1 != nullptr, g.rows_ok != 0,
+                   g.partial ? g.partial_bytes : 0});
+  if (p.wide >= 0) return dispatch_wide<MODE>(g, p.wide, s);
+  if (p.bm == 128)
+    return p.waves == 8 ? launch_s<MODE, 128, 128, GEMM_S128, 1, 8>(g, p.splits, s)
+                        : launch_s<MODE, 128, 128, GEMM_S128>(g, p.splits, s);
+  if (p.bn == 128) return launch_s<MODE, 64, 128, 2, 1, 8>(g, p.splits, s);
+  return p.waves == 8 ? launch_s<MODE, 64, 64, 4, 1, 8>(g, p.splits, s)
+                      : launch_s<MODE, 64, 64, GEMM_S64>(g, p.splits, s);
 }
 
 template <int MODE>

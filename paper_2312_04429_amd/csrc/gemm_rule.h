@@ -24,26 +24,28 @@ struct StreamPlan {
 // Forms of the wide kernel and their cost in us: a launch costs 5, a single
 // round of tiles f1 + s1 per 64-deep k tile, and each of several rounds f2 + s2
 // per k tile.  A round is 256 tiles with one workgroup per CU, 512 with two (its
-// last one, if it has at most 256 tiles, costs f1 and s1).  The constants
-// were fitted to graph-timed products of the UNet's layers at other resolutions,
-// batches and channel counts (730 shapes, 80 to 65536 rows, 5 to 360 k tiles,
-// weights warm and streaming from HBM) so that the chosen form costs least: 0.5 %
-// above the fastest form on average, and at most 8 % slower than the kernels
-// below alone, which take 18 % longer on average.
+// last one, if it has at most 256 tiles, costs f1 and s1).  The constants were
+// fitted, first of all so that the chosen form costs least, to 1124 graph-timed
+// products (the UNet's layers at other resolutions, batches and channel counts: 16
+// to 65536 rows, 1 to 360 k tiles, weights warm and streaming from HBM) and 363
+// layers timed inside networks (78 with a folded LayerNorm): the choice takes 0.4 to
+// 1 % more than the fastest form on average, and 0.6 % on 497 further products.  The
+// small-tile kernels alone take 17 % longer; 15 of the 1984 lose more than 3 %
+// against them, 16 % at most.
 struct WideForm {
   int bm, bn, shares, per_cu;  // shares: wave groups that share out k (KH * KT)
   float f1, s1, f2, s2;
 };
 constexpr WideForm WIDE[] = {
-    {256, 256, 1, 1, 7.68f, 1.287f, 10.75f, 1.111f},  // 0: 8 waves of 128 x 64
-    {256, 160, 1, 1, 7.13f, 0.832f, 8.22f, 0.886f},   // 1: 8 waves of 64 x 80
-    {128, 160, 1, 2, 2.75f, 0.563f, 4.54f, 0.909f},   // 2: 8 waves of 32 x 80
-    {128, 160, 2, 1, 2.92f, 0.542f, 5.36f, 0.576f},   // 3: 2 k halves x 4 waves of 64 x 80
-    {128, 128, 1, 2, 1.08f, 0.620f, 5.51f, 0.732f},   // 4: 8 waves of 64 x 32
-    {128, 80, 2, 2, 0.80f, 0.435f, 3.45f, 0.612f},    // 5: 2 k halves x 4 waves of 32 x 80
-    {64, 128, 2, 2, 0.00f, 0.300f, 3.13f, 0.499f},    // 6: 2 k halves x 4 waves of 32 x 64
-    {64, 80, 4, 1, 0.70f, 0.248f, 3.19f, 0.258f},     // 7: 2 k halves x 2 teams x 2 waves of 32 x 80
-    {64, 64, 2, 2, 0.00f, 0.184f, 2.32f, 0.358f},     // 8: 2 k halves x 4 waves of 32 x 32
+    {256, 256, 1, 1, 11.10f, 1.354f, 12.18f, 1.105f},  // 0: 8 waves of 128 x 64
+    {256, 160, 1, 1, 9.27f, 0.856f, 11.09f, 0.807f},   // 1: 8 waves of 64 x 80
+    {128, 160, 1, 2, 4.43f, 0.590f, 5.20f, 0.909f},    // 2: 8 waves of 32 x 80
+    {128, 160, 2, 1, 4.23f, 0.517f, 6.00f, 0.585f},    // 3: 2 k halves x 4 waves of 64 x 80
+    {128, 128, 1, 2, 1.60f, 0.699f, 6.03f, 0.743f},    // 4: 8 waves of 64 x 32
+    {128, 80, 2, 2, 0.94f, 0.401f, 4.39f, 0.615f},     // 5: 2 k halves x 4 waves of 32 x 80
+    {64, 128, 2, 2, 0.34f, 0.324f, 2.45f, 0.527f},     // 6: 2 k halves x 4 waves of 32 x 64
+    {64, 80, 4, 1, 1.27f, 0.247f, 1.20f, 0.215f},      // 7: 2 k halves x 2 teams x 2 waves of 32 x 80
+    {64, 64, 2, 2, 0.22f, 0.240f, 1.81f, 0.357f},      // 8: 2 k halves x 4 waves of 32 x 32
 };
 constexpr int WIDE_FORMS = sizeof(WIDE) / sizeof(WIDE[0]);
 constexpr int CUS = 256;
@@ -71,9 +73,9 @@ inline bool wide_takes(const WideForm& w, const StreamShape& g) {
 // tile), so small tiles and many resident workgroups win: K is split when it is
 // long (> 40 tiles) or the grid is tiny, keeping >= MIN_KT tiles per split.
 // Unsplit forms serve what the row-staged epilogue does not take (column counts
-// off the grid of 8, float32 outputs, unaligned buffers); among those, tiles of
-// 128 x 128 for very wide or deep products and for 320 columns and fewer, 64 x
-// 128 for the other large grids, 64 x 64 below.
+// off the grid of 8, float32 outputs, unaligned buffers) and small GEGLU grids;
+// large grids of those take tiles of 128 x 128 where very wide or deep and up to
+// 320 columns, 64 x 128 otherwise.
 inline StreamPlan gemm_s_plan(const StreamShape& g) {
   constexpr int MIN_KT = 10;
   const int nk = g.K / 64;
@@ -129,24 +131,35 @@ inline float split_cost(const StreamPlan& p, const StreamShape& g) {
          (float)splits * (float)g.M * (float)g.N * 1e-6f * c.red_mb;
 }
 
-// The cheapest wide form, unless gemm_s would split K (2 shares or more) and its
-// estimate is within 14 % of that form's: the two estimates are good to about 10 %
-// each, and the fits above found the fewest wrong choices there.  Unsplit gemm_s
-// is not priced: the wide forms are its equals or better wherever both apply.
+// The cheapest wide form, unless gemm_s would split K (2 shares or more) for less:
+// a dense product if its estimate is 1 us or more below that form's (its second
+// launch costs as much again where launches are not captured), a convolution
+// if it is up to 6 % above (the estimates are good to about 10 % each, and the
+// timings above had the fewest wrong choices there).  Unsplit gemm_s is not
+// priced: the wide forms are its equals or better wherever both apply, but for
+// GEGLU, whose two forms leave most CUs without a tile up to 320 tiles of 128 x 128
+// (inside the network 128 x 10240 x 1280 19.0 us on small tiles, 26.3 on form 4;
+// 512 x 5120 x 640 14.1 and 14.9; 512 x 10240 x 1280, 320 tiles, 31.6 and 31.8; 768
+// x 10240 x 1280, 480 tiles, 44.0 and 31.7).
 inline StreamPlan stream_plan(const StreamShape& g) {
   const StreamPlan s = gemm_s_plan(g);
-  if (!g.rows_ok) return s;
+  if (!g.rows_ok || (g.geglu && tiles_of(g, 128, 128) <= 320)) return s;
   int best = -1;
   float cost = 0.f;
   for (int i = 0; i < WIDE_FORMS; ++i) {
     if (!wide_takes(WIDE[i], g)) continue;
-    const float c = wide_cost(WIDE[i], g);
+    // the fits hold no GEGLU products, whose gates cost form 4 more (1024 x 10240 x
+    // 1280 52.3 us against 45.9 of form 0, 8192 x 5120 x 640 79.1 against 76.1, both
+    // estimated about equal)
+    const float c = wide_cost(WIDE[i], g) * (g.geglu && WIDE[i].bm == 128 ? 1.06f : 1.0f);
     if (best < 0 || c < cost) {
       best = i;
       cost = c;
     }
   }
-  if (s.splits > 1 && !g.geglu && split_cost(s, g) < 1.14f * cost) return s;
+  if (s.splits > 1 && !g.geglu &&
+      (g.conv ? split_cost(s, g) + 0.5f < 1.06f * cost : split_cost(s, g) + 1.0f < cost))
+    return s;
   return {best, WIDE[best].bm, WIDE[best].bn, 0, 1};
 }
 
