@@ -450,7 +450,7 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   __shared__ int64_t ri[NWV];
   __shared__ int64_t ids[256];
   __shared__ int surv[256];
-  __shared__ int n_surv;
+  __shared__ int n_surv, n_nan;
   const int jp = blockIdx.x, ch = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int j = jp / nprobe;
   const int l = probed[jp];
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   }
   const char* rows = (const char*)lrows + p0 * d * (bf ? 2 : 4);
   load_query(qd, q + (int64_t)j * d, d);
-  if (t == 0) n_surv = 0;
+  if (t == 0) n_surv = n_nan = 0;
   if (t < 256) ids[t] = t < nrows ? perm[p0 + t] : -1;
   __syncthreads();
   double qq = 0.0;
@@ -532,14 +532,17 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   const double scale = 0x1p-40 * sqrt(qq) * (1.0 + 0x1p-40);
   // the block's best canonical score is at least the largest dot - tol
   double lo = -INFINITY;
-  if (t < nrows) lo = fast[t] - (scale * tols[t] + 0x1p-1000);
+  if (t < nrows) {
+    lo = fast[t] - (scale * tols[t] + 0x1p-1000);
+    // the products decide whether a sum is a number, whatever its order
+    if (isnan(fast[t])) n_nan = 1;
+  }
   for (int o = 32; o > 0; o >>= 1) lo = fmax(lo, __shfl_xor(lo, o, 64));
   if (lane == 0) rs[wave] = lo;
   __syncthreads();
   for (int w = 0; w < NWV; ++w) lo = fmax(lo, rs[w]);
-  // the products decide whether a sum is a number, whatever its order; a bound that is
-  // not a number rules nothing out
-  const bool any_nan = __syncthreads_or(t < nrows && isnan(fast[t])) != 0;
+  const bool any_nan = n_nan != 0;
+  // a bound that is not a number rules nothing out
   if (t < nrows && (any_nan || !(fast[t] + (scale * tols[t] + 0x1p-1000) < lo)))
     surv[atomicAdd(&n_surv, 1)] = t;
   __syncthreads();
