@@ -1722,14 +1722,7 @@ hipError_t gemm_launch_one(const GemmArgs& gin, hipStream_t s) {
   g.vec_ok = (g.N % 4 == 0) && (g.ldo % 4 == 0) && al(g.out, g.out_f32 ? 16 : 8) &&
              (!g.bias || al(g.bias, 16)) &&
              (!g.residual || ((g.ld_res % 4 == 0) && al(g.residual, 8)));
-  // the row-staged epilogue: 8 float16 columns (or 8 tokens of a transposed
-  // column) per thread as one 16-byte access
-  g.rows_ok = g.vec_ok && !g.out_f32 && g.M < (int64_t(1) << 31) && g.N % (g.geglu ? 32 : 8) == 0 &&
-              g.ldo % 8 == 0 && al(g.out, 16) && (!g.rowvec || g.rows_div < (int64_t(1) << 31)) &&
-              (!g.residual || (g.ld_res % 8 == 0 && al(g.residual, 16))) &&
-              (!g.vt || (!g.geglu && g.M % 8 == 0 && g.vt_col0 % 8 == 0 && g.vt_ld % 8 == 0 &&
-                         g.vt_div % 8 == 0 && g.vt_div < (int64_t(1) << 31) &&
-                         g.vt_stride % 8 == 0 && al(g.vt, 16)));
+  g.rows_ok = row_epilogue_ok(g);
   return g.conv ? dispatch<1>(g, s) : dispatch<0>(g, s);
 }
 

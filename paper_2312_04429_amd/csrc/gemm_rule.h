@@ -14,6 +14,23 @@ struct StreamShape {
   size_t partial_bytes;  // split-K scratch, 0 without
 };
 
+// Whether the row-staged epilogue (epilogue_rows) takes a product: 8 float16
+// columns, or 8 tokens of a transposed column, move as one 16-byte access.  It adds
+// neither a row vector nor a residual to transposed columns; the other epilogues
+// add the row vector there, so a product with both is theirs.  Args: GemmArgs
+// (vec_ok filled in).
+template <typename Args>
+inline bool row_epilogue_ok(const Args& g) {
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  constexpr int64_t LIMIT = int64_t(1) << 31;
+  return g.vec_ok && !g.out_f32 && g.M < LIMIT && g.N % (g.geglu ? 32 : 8) == 0 &&
+         g.ldo % 8 == 0 && aligned(g.out) && (!g.rowvec || g.rows_div < LIMIT) &&
+         (!g.residual || (g.ld_res % 8 == 0 && aligned(g.residual))) &&
+         (!g.vt || (!g.geglu && !g.rowvec && g.M % 8 == 0 && g.vt_col0 % 8 == 0 &&
+                    g.vt_ld % 8 == 0 && g.vt_div % 8 == 0 && g.vt_div < LIMIT &&
+                    g.vt_stride % 8 == 0 && aligned(g.vt)));
+}
+
 // wide: index into WIDE (one share of K; waves unused), or -1: gemm_s with bm x
 // bn tiles, `waves` waves and `splits` shares of K (the launcher rounds the shares
 // to whole k tiles, which can leave fewer).

@@ -215,3 +215,39 @@ def test_products_that_cannot_split(stream_rule):
             for ln in (0, 1):
                 p = stream_rule(M, N, K, 0, ln=ln, rows_ok=0)
                 assert p.wide == -1 and (p.splits == 1 or not ln)
+
+
+class Args(C.Structure):
+    """The fields of a product that the row-staged epilogue's gate reads."""
+    _fields_ = ([("M", C.c_longlong), ("rows_div", C.c_longlong), ("vt_ld", C.c_longlong),
+                 ("vt_div", C.c_longlong), ("vt_stride", C.c_longlong)] +
+                [(n, C.c_void_p) for n in ("out", "rowvec", "residual", "vt")] +
+                [(n, C.c_int) for n in ("N", "ldo", "ld_res", "vt_col0", "vec_ok", "out_f32", "geglu")])
+
+
+def test_row_epilogue_gate(tmp_path_factory):
+    """What the row-staged epilogue cannot do goes elsewhere: transposed columns with a row vector
+    (it adds none to them) or with GEGLU, float32 outputs, and anything off its 16-byte pieces."""
+    lib = _compiled(tmp_path_factory, "gate", """
+#include "gemm_rule.h"
+struct Args {
+  long long M, rows_div, vt_ld, vt_div, vt_stride;
+  void *out, *rowvec, *residual, *vt;
+  int N, ldo, ld_res, vt_col0, vec_ok, out_f32, geglu;
+};
+extern "C" int ok(const Args* a) { return nv::row_epilogue_ok(*a); }
+""")
+    base = dict(M=512, N=960, ldo=640, ld_res=640, vec_ok=1, out=0x1000, rows_div=1)
+    vt = dict(vt=0x2000, vt_col0=640, vt_ld=512, vt_div=256, vt_stride=256)
+    ok = lambda **over: bool(lib.ok(C.byref(Args(**dict(base, **over)))))
+    assert ok() and ok(**vt) and ok(residual=0x3000) and ok(rowvec=0x4004, rows_div=256)
+    assert ok(geglu=1) and ok(residual=0x3000, **vt)
+    assert not ok(rowvec=0x4000, rows_div=256, **vt)
+    assert not ok(geglu=1, **vt)
+    for bad in (dict(vec_ok=0), dict(out_f32=1), dict(M=1 << 31), dict(N=956), dict(ldo=644),
+                dict(out=0x1008), dict(residual=0x3008), dict(residual=0x3000, ld_res=644),
+                dict(geglu=1, N=944), dict(rowvec=0x4000, rows_div=1 << 31)):
+        assert not ok(**bad), bad
+    for bad in (dict(M=511), dict(vt=0x2008), dict(vt_col0=644), dict(vt_ld=508), dict(vt_div=252),
+                dict(vt_stride=252)):
+        assert not ok(**dict(vt, **bad)), bad
