@@ -1613,7 +1613,8 @@ hipError_t launch_w_t(const GemmArgs& g, hipStream_t s) {
   const double bytes = (double)g.bytes1 + g.bytes2 + (double)g.N * g.K * 2 +
                        (double)g.M * (g.geglu ? g.N / 2 : g.N) * 2;
   const TraceEv ev =
-      trace_begin(fam, flops, bytes, TraceShape{g.M, g.N, g.K, BM * 10000 + BN * 10 + 1});
+      trace_begin(fam, flops, bytes,
+                  TraceShape{g.M, g.N, g.K, KH * KT * 100000000ll + BM * 10000 + BN * 10 + 1});
   hipExtLaunchKernelGGL((gemm_w<MODE, BM, BN, WGM, WGN, KH, KT, STAGES, LN>), grid, dim3(NW * 64),
                         (uint32_t)lds, s, ev.a, ev.b, 0u, g);
   return hipGetLastError();

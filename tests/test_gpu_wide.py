@@ -1,6 +1,9 @@
 """GPU parity of the wide GEMM forms (whole-chip tiles, k halves and k teams, the row-staged
 epilogue) at the edges of their tiles: ragged rows and columns, one k tile (a team without
-one), odd k tile counts, two sources, strided and upsampling convolutions."""
+one), odd k tile counts, two sources, strided and upsampling convolutions; and, through small
+networks of ragged row counts, the epilogues that have no call of their own (folded LayerNorm,
+transposed columns, GEGLU, the time embedding's row vector).  The tests that name a form check in
+the launch trace that it ran."""
 import numpy as np
 import pytest
 import torch
@@ -63,3 +66,118 @@ def test_conv_forms(B, H, W, C1, C2, Co, stride, up):
     ref = conv(x.double(), w.double(), b.double())
     mag = conv(x.double().abs(), w.double().abs(), b.double().abs())
     _check(got, ref, mag, 9 * C)
+
+
+# (tile rows, tile columns, wave groups that share out k) of the forms, in the rule's order
+FORMS = [(256, 256, 1), (256, 160, 1), (128, 160, 1), (128, 160, 2), (128, 128, 1), (128, 80, 2),
+         (64, 128, 2), (64, 80, 4), (64, 64, 2)]
+
+
+def _code(form):
+    bm, bn, shares = FORMS[form]
+    return shares * 100_000_000 + bm * 10_000 + bn * 10 + 1
+
+
+def _traced(P, call):
+    P.nv_trace_enable(3, 8192)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+    finally:
+        P.nv_trace_disable()
+    return out, [r[1] for r in P.nv_trace_records()]
+
+
+@pytest.mark.parametrize("form,M,N,K", [
+    (0, 20552, 648, 192), (1, 21797, 264, 5120), (2, 16652, 264, 192), (3, 16548, 136, 320),
+    (4, 16412, 88, 64), (5, 16396, 8, 64), (6, 8283, 72, 192), (7, 517, 4360, 192), (8, 1, 8, 64)])
+def test_linear_each_form(form, M, N, K):
+    import paper_2312_04429_amd as P
+    print(f"wide linear form {form} M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn(M, K, generator=g, device="cuda").half()
+    w = (0.05 * torch.randn(N, K, generator=g, device="cuda")).half()
+    b = torch.randn(N, generator=g, device="cuda")
+    r = torch.randn(M, N, generator=g, device="cuda").half()
+    got, ran = _traced(P, lambda: P.nv_op_linear(x, w, b, r))
+    assert [v for _, _, _, v in ran] == [_code(form)]
+    ref = x.double() @ w.double().T + b.double() + r.double()
+    mag = x.double().abs() @ w.double().abs().T + b.double().abs() + r.double().abs()
+    _check(got.double().cpu().numpy(), ref.cpu().numpy(), mag.cpu().numpy(), K)
+
+
+@pytest.mark.parametrize("form,B,H,W,C1,C2,Co,stride,up", [
+    (0, 4, 53, 58, 64, 0, 168, 1, 1), (0, 8, 43, 72, 64, 64, 416, 1, 0),
+    (0, 8, 66, 68, 64, 0, 1640, 2, 0), (1, 3, 61, 70, 320, 128, 264, 1, 1),
+    (1, 8, 62, 68, 320, 128, 1944, 2, 0), (2, 6, 45, 31, 64, 64, 144, 1, 1),
+    (2, 8, 52, 58, 64, 0, 1288, 2, 0), (3, 8, 67, 31, 64, 64, 136, 1, 0),
+    (3, 8, 56, 60, 64, 0, 536, 2, 0), (4, 4, 46, 34, 64, 64, 168, 1, 1),
+    (4, 8, 60, 52, 64, 0, 904, 2, 0), (5, 4, 57, 72, 64, 64, 8, 1, 0),
+    (5, 8, 70, 66, 64, 0, 136, 2, 0), (5, 3, 36, 38, 64, 0, 8, 1, 1),
+    (6, 4, 35, 15, 64, 64, 88, 1, 1), (6, 8, 72, 70, 64, 0, 72, 2, 0),
+    (7, 1, 50, 42, 64, 64, 72, 1, 1), (7, 8, 70, 60, 128, 0, 72, 2, 0),
+    (8, 1, 4, 4, 64, 64, 8, 2, 0)])
+def test_conv_each_form(form, B, H, W, C1, C2, Co, stride, up):
+    import paper_2312_04429_amd as P
+    print(f"wide conv form {form} {B}x{H}x{W} {C1}+{C2}->{Co} s{stride} u{up}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(H * W + Co)
+    C = C1 + C2
+    x = torch.randn(B, H, W, C, generator=g, device="cuda").half()
+    w = (torch.randn(Co, 3, 3, C, generator=g, device="cuda") / (9 * C) ** 0.5).half()
+    b = torch.randn(Co, generator=g, device="cuda")
+    x1, x2 = x[..., :C1].contiguous(), x[..., C1:].contiguous() if C2 else None
+    got, ran = _traced(P, lambda: P.nv_op_conv3x3(x1, w, b, stride=stride, upsample=bool(up),
+                                                  x2=x2))
+    assert [v for _, _, _, v in ran] == [_code(form)]
+    a = x.permute(0, 3, 1, 2)
+    if up:
+        a = a.repeat_interleave(2, 2).repeat_interleave(2, 3)
+    a = torch.nn.functional.pad(a, (1, 1, 1, 1))
+    ho, wo = got.shape[1:3]
+    wf = w.reshape(Co, 9 * C).double()
+    for i in range(B):  # one sample's taps at a time, in the weights' order
+        cols = torch.stack([a[i, :, ky:ky + stride * (ho - 1) + 1:stride,
+                              kx:kx + stride * (wo - 1) + 1:stride].reshape(C, ho * wo)
+                            for ky in range(3) for kx in range(3)]).reshape(9 * C, ho * wo).double()
+        ref = (wf @ cols).T + b.double()
+        mag = (wf.abs() @ cols.abs()).T + b.double().abs()
+        _check(got[i].reshape(ho * wo, Co).double().cpu().numpy(), ref.cpu().numpy(),
+               mag.cpu().numpy(), 9 * C)
+
+
+# forms of the self-attention's q | k | v (folded LayerNorm, V transposed), of the cross-attention's
+# q (folded LayerNorm) and of the GEGLU product (folded LayerNorm) over 1496 tokens a row
+@pytest.mark.parametrize("C,heads,B,qkv,q,ff1", [(128, 4, 2, 5, 8, 4), (128, 4, 8, 6, 4, 4),
+                                                 (320, 8, 4, 4, 3, 0), (320, 8, 8, 2, 2, 0)])
+def test_network_epilogues(C, heads, B, qkv, q, ff1):
+    import paper_2312_04429_amd as P
+    import synth
+    from oracle import schedule
+    from oracle import unet as U
+    cfg = synth.unet_config("tiny", H=88, W=68, ch=(64, C), n_heads=heads, mid_depth=0)
+    w = dict(synth.make_weights(cfg, 0))
+    rng = np.random.default_rng(C + B)
+    for k in w:  # LayerNorms whose gains and shifts differ from channel to channel
+        if ".ln" in k:
+            w[k] = (w[k] + rng.uniform(-0.5, 0.5, w[k].shape)).astype(np.float32)
+    print(f"wide network C={C} B={B}", flush=True)
+    net = P.NvUNet(cfg, w)
+    try:
+        x = synth.make_latents(B, 4, 88, 68, 7)
+        cond, unc = (synth.make_contexts(B, cfg["ctx_len"], cfg["ctx_dim"], s) for s in (11, 12))
+        t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        (eu, ec), ran = _traced(P, lambda: net.nv_unet_eps(t(x), [9] * B, t(cond), t(unc),
+                                                           sched=(1000, 20, 0.00085, 0.012)))
+        M = 2 * B * 44 * 34
+        seen = {(n, k): v for m, n, k, v in ran if m == M}
+        assert seen[3 * C, C] == _code(qkv)
+        assert seen[8 * C, C] == _code(ff1)
+        assert _code(q) in [v for m, n, k, v in ran if (m, n, k) == (M, C, C)]
+        ora = U.UNet(cfg, w)
+        ts = schedule.timesteps(20, 1000)[9]
+        for b in (0, B - 1):
+            for got, ctx in ((eu, unc), (ec, cond)):
+                # the float16 bar of the network's other tests
+                assert np.abs(got[b].cpu().numpy() - ora(x[b], ts, ctx[b])).max() <= 1e-2
+    finally:
+        net.close()
