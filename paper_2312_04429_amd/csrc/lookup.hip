@@ -1243,7 +1243,8 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
   if (T > 0) {
     if (many) {
       const size_t lds = (size_t)MANY_R * 16 * dp * 2 + 8 * 4;
-      const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d);
+      const TraceEv ev =
+          trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d, TraceShape{m, n, d, nbw});
       const uint16_t* cb = (const uint16_t*)cache;
       const dim3 grid((unsigned)std::min(T, 256), (unsigned)ceil_div(m, 64 * nbw));
 #define NV_MANY1(ns, w)                                                                         \
@@ -1275,7 +1276,8 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
 #undef NV_RR
       }
       NV_HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d);
+      const TraceEv ev =
+          trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d, TraceShape{m, n, d, nbw});
       const uint16_t* cb = (const uint16_t*)cache;
       switch (dp / 32) {
 #define NV_RR(ns)                                                                          \
@@ -1291,12 +1293,14 @@ int32_t lookup_run(const float* queries, int32_t m, const void* cache, int32_t c
       const size_t lds = (size_t)QB * dp * 2 + (size_t)2 * QB * SS_WIDE * 4 + TILE * 4;
       NV_HIP_TRY(hipFuncSetAttribute((const void*)lk_scan_bf16_wide,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d);
+      const TraceEv ev =
+          trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 2.0 * (double)n * d, TraceShape{m, n, d, nbw});
       hipExtLaunchKernelGGL(lk_scan_bf16_wide, dim3(T), dim3(256), (uint32_t)lds, s, ev.a, ev.b,
                             0u, (const uint16_t*)cache, n, (int)d, (int)m, ws);
       NV_LAUNCH_CHECK("lk_scan_bf16_wide");
     } else {
-      const TraceEv ev = trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 4.0 * (double)n * d);
+      const TraceEv ev =
+          trace_begin(NV_FAM_SCAN, 2.0 * m * (double)n * d, 4.0 * (double)n * d, TraceShape{m, n, d, 0});
       // two query blocks per pass where they fit: each pass reads the rows
       auto lds_of = [&](int qn) {
         return (size_t)qn * QB * f32_qrow(d) * 4 + (size_t)8 * qn * QB * 4 + TILE * 4;

@@ -11,8 +11,9 @@ struct TraceEv {
   hipEvent_t a = nullptr, b = nullptr;
 };
 // Shape of a traced launch: matrix products (M, N, K, tile code BM*10000 +
-// BN*10 + splits), attention (S, L, heads*dh, head dim*10000 + QB*1000 + KB),
-// scans (m, n, d, 0).
+// BN*10 + splits, plus 10^8 times the wave groups that share out k for the wide
+// kernel's forms), attention (S, L, heads*dh, head dim*10000 + QB*1000 + KB),
+// scans (m, n, d, query blocks per wave of the scan that holds them, else 0).
 struct TraceShape {
   int64_t m = 0, n = 0, k = 0, variant = 0;
 };
