@@ -136,8 +136,9 @@ def unet_flops_per_row(cfg):
 def kernel_source_sha(family):
     """Hash of the sources that define a kernel family (to tie stored counters to code)."""
     import hashlib
-    files = {"conv3x3_igemm": ["gemm.hip", "gemm.h"], "linear_gemm": ["gemm.hip", "gemm.h"],
-             "attention": ["attention.hip"], "cache_scan": ["lookup.hip"]}[family]
+    gemm = ["gemm.hip", "gemm.h", "gemm_rule.h", "gelu.h"]
+    files = {"conv3x3_igemm": gemm, "linear_gemm": gemm, "attention": ["attention.hip"],
+             "cache_scan": ["lookup.hip", "lookup_rule.h"]}[family]
     h = hashlib.sha256()
     for f in files:
         h.update(open(os.path.join(ROOT, "paper_2312_04429_amd", "csrc", f), "rb").read())

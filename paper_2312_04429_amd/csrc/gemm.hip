@@ -15,14 +15,20 @@
 // (16 "a" rows, 16 "g" rows) and output column j of group j/16 is
 // a * GELU_erf(g).  Output float16 or float32.
 //
-// Tiling: BM x BN x 64 block tile, 4 waves in 2 x 2, each wave (BM/2) x
-// (BN/2) as 16x16 MFMA blocks.  Global -> registers -> LDS double buffer, one
-// barrier per 64-deep k tile; LDS rows are padded to 144 bytes so the 16
-// rows read by a quarter-wave land in distinct 16-byte bank groups (9r mod 16
-// is a permutation).  The conv loader walks (tap, ci) incrementally: no
-// integer division in the k loop.  Small problems split K across workgroups;
-// the float32 partials are summed in a fixed order by a second kernel that
-// applies the epilogue (deterministic).
+// Three kernels:
+//   gemm_f16  any K and channel counts in multiples of 8: global -> registers ->
+//             LDS double buffer, 4 waves in 2 x 2, each (BM/2) x (BN/2) as 16x16
+//             MFMA blocks, one barrier per 64-deep k tile; LDS rows are padded to 144
+//             bytes so the 16 rows read by a quarter-wave land in distinct 16-byte
+//             bank groups (9r mod 16 is a permutation).  The conv loader walks (tap,
+//             ci) incrementally: no integer division in the k loop.
+//   gemm_s    every 64-deep k tile in one source and tap: global -> LDS without
+//             registers, small wave tiles; what it runs now is split K, products
+//             whose outputs the row-staged epilogue cannot take, and small GEGLU grids.
+//   gemm_w    the same products otherwise: larger wave tiles, or k shared out over
+//             wave groups, and the row-staged epilogue.
+// gemm_rule.h chooses between the last two.  Split K leaves float32 partials, summed
+// in a fixed order by splitk_reduce, which applies the epilogue (deterministic).
 #include <algorithm>
 #include <type_traits>
 

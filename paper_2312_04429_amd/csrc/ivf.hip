@@ -15,11 +15,14 @@
 //           sorted by list (a stable counting sort: ascending rows within a list),
 //           list offsets, and a copy of the rows in list order, so a probe
 //           reads one contiguous block.
-//   search: centroid scores per (query, list); the best nprobe lists per query
-//           (a bitonic sort in one workgroup); every probed row rescored
-//           canonically (rows staged through LDS with coalesced loads, one
-//           thread per row); per-(query, probe, chunk) best rows merged in a
-//           final pass; float32 similarity and the selector's K.
+//   search: canonical centroid scores per (query, list) (products in parallel, the
+//           ordered sum by one lane per centroid); the best nprobe lists per query (a
+//           radix select in one workgroup); per (query, probe, 256 rows) the best
+//           row: float64 dots in another order, each within 2^-40 |q| |c| of the
+//           canonical score (2 d 2^-53 |q| |c| for any two orders of exact products, d
+//           <= 2048), rule out the rows that cannot be best, and those left are
+//           summed canonically; a final pass merges the blocks' rows; float32
+//           similarity and the selector's K.
 #include <algorithm>
 #include <cmath>
 #include <vector>

@@ -2,9 +2,9 @@
 // selector (Sec. 5.3.1: similarity -> K by strictly-exceeded thresholds).
 //
 // Exact top-1 in two phases:
-//   1. scan: every cache row is streamed once.  bf16 caches go through bf16
-//      matrix cores (queries rounded to bf16, fp32 accumulation), f32 caches
-//      through fp32 FMAs.  For each (row i, query q) the scan score s~ obeys
+//   1. scan: every cache row is streamed (once, or once per pass of queries).  bf16
+//      caches go through bf16 matrix cores (queries rounded to bf16, fp32
+//      accumulation), f32 caches through fp32 ones.  For each (row i, query q) the scan score s~ obeys
 //      |s~ - s64| <= |c_i| * E_q, with E_q = |q - bf16(q)| + (2 d 2^-24 +
 //      d 2^-52) |q~| (Cauchy-Schwarz on the rounding of q plus the worst-case
 //      accumulation error of any summation order, plus the float64 canonical
@@ -15,10 +15,10 @@
 //   2. select: per query, L = max_t (M_tq - N_t E_q) is a lower bound on the
 //      best canonical score, and every row that can reach it lies in a tile
 //      with M_tq + N_t E_q >= L (found by lk_finish; past its tile limit by
-//      lk_bound and lk_mark).  lk_finish reads those tiles again: a float64 dot in another summation order
-//      discards rows that provably cannot reach L; the rest are rescored with
-//      the canonical float64 left-to-right dot product; the maximum with the
-//      lowest index wins; its float32 rounding goes through the thresholds.
+//      lk_bound and lk_mark).  lk_finish reads those tiles again: a float64 dot in
+//      another summation order discards rows that provably cannot reach L; the rest
+//      are rescored with the canonical float64 left-to-right dot product; the maximum
+//      with the lowest index wins; its float32 rounding goes through the thresholds.
 #include <algorithm>
 #include <cmath>
 #include <mutex>

@@ -16,10 +16,10 @@ import json
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-FAMS = {"conv3x3_igemm": (("gemm_f16<1", "gemm_s<1", "gemm_w<1"), ["gemm.hip", "gemm.h"]),
-        "linear_gemm": (("gemm_f16<0", "gemm_s<0", "gemm_w<0"), ["gemm.hip", "gemm.h"]),
+FAMS = {"conv3x3_igemm": (("gemm_f16<1", "gemm_s<1", "gemm_w<1"), ["gemm.hip", "gemm.h", "gemm_rule.h", "gelu.h"]),
+        "linear_gemm": (("gemm_f16<0", "gemm_s<0", "gemm_w<0"), ["gemm.hip", "gemm.h", "gemm_rule.h", "gelu.h"]),
         "attention": (("attn_f16",), ["attention.hip"]),
-        "cache_scan": (("lk_scan",), ["lookup.hip"])}
+        "cache_scan": (("lk_scan",), ["lookup.hip", "lookup_rule.h"])}
 CALIB_BYTES = float(1 << 30)
 
 
