@@ -2,8 +2,9 @@
 epilogue) at the edges of their tiles: ragged rows and columns, one k tile (a team without
 one), odd k tile counts, two sources, strided and upsampling convolutions; and, through small
 networks of ragged row counts, the epilogues that have no call of their own (folded LayerNorm,
-transposed columns, GEGLU, the time embedding's row vector).  The tests that name a form check in
-the launch trace that it ran."""
+transposed columns, GEGLU, the time embedding's row vector).  The small-tile kernel's forms follow,
+unsplit for column counts that the row-staged epilogue does not take, and split.  The tests that
+name a form check in the launch trace that it ran."""
 import numpy as np
 import pytest
 import torch
@@ -88,38 +89,22 @@ def _traced(P, call):
     return out, [r[1] for r in P.nv_trace_records()]
 
 
-@pytest.mark.parametrize("form,M,N,K", [
-    (0, 20552, 648, 192), (1, 21797, 264, 5120), (2, 16652, 264, 192), (3, 16548, 136, 320),
-    (4, 16412, 88, 64), (5, 16396, 8, 64), (6, 8283, 72, 192), (7, 517, 4360, 192), (8, 1, 8, 64)])
-def test_linear_each_form(form, M, N, K):
+def _linear(code, M, N, K):
     import paper_2312_04429_amd as P
-    print(f"wide linear form {form} M={M} N={N} K={K}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(M + N)
     x = torch.randn(M, K, generator=g, device="cuda").half()
     w = (0.05 * torch.randn(N, K, generator=g, device="cuda")).half()
     b = torch.randn(N, generator=g, device="cuda")
     r = torch.randn(M, N, generator=g, device="cuda").half()
     got, ran = _traced(P, lambda: P.nv_op_linear(x, w, b, r))
-    assert [v for _, _, _, v in ran] == [_code(form)]
+    assert [v for _, _, _, v in ran] == [code]
     ref = x.double() @ w.double().T + b.double() + r.double()
     mag = x.double().abs() @ w.double().abs().T + b.double().abs() + r.double().abs()
     _check(got.double().cpu().numpy(), ref.cpu().numpy(), mag.cpu().numpy(), K)
 
 
-@pytest.mark.parametrize("form,B,H,W,C1,C2,Co,stride,up", [
-    (0, 4, 53, 58, 64, 0, 168, 1, 1), (0, 8, 43, 72, 64, 64, 416, 1, 0),
-    (0, 8, 66, 68, 64, 0, 1640, 2, 0), (1, 3, 61, 70, 320, 128, 264, 1, 1),
-    (1, 8, 62, 68, 320, 128, 1944, 2, 0), (2, 6, 45, 31, 64, 64, 144, 1, 1),
-    (2, 8, 52, 58, 64, 0, 1288, 2, 0), (3, 8, 67, 31, 64, 64, 136, 1, 0),
-    (3, 8, 56, 60, 64, 0, 536, 2, 0), (4, 4, 46, 34, 64, 64, 168, 1, 1),
-    (4, 8, 60, 52, 64, 0, 904, 2, 0), (5, 4, 57, 72, 64, 64, 8, 1, 0),
-    (5, 8, 70, 66, 64, 0, 136, 2, 0), (5, 3, 36, 38, 64, 0, 8, 1, 1),
-    (6, 4, 35, 15, 64, 64, 88, 1, 1), (6, 8, 72, 70, 64, 0, 72, 2, 0),
-    (7, 1, 50, 42, 64, 64, 72, 1, 1), (7, 8, 70, 60, 128, 0, 72, 2, 0),
-    (8, 1, 4, 4, 64, 64, 8, 2, 0)])
-def test_conv_each_form(form, B, H, W, C1, C2, Co, stride, up):
+def _conv(code, B, H, W, C1, C2, Co, stride, up):
     import paper_2312_04429_amd as P
-    print(f"wide conv form {form} {B}x{H}x{W} {C1}+{C2}->{Co} s{stride} u{up}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(H * W + Co)
     C = C1 + C2
     x = torch.randn(B, H, W, C, generator=g, device="cuda").half()
@@ -128,7 +113,7 @@ def test_conv_each_form(form, B, H, W, C1, C2, Co, stride, up):
     x1, x2 = x[..., :C1].contiguous(), x[..., C1:].contiguous() if C2 else None
     got, ran = _traced(P, lambda: P.nv_op_conv3x3(x1, w, b, stride=stride, upsample=bool(up),
                                                   x2=x2))
-    assert [v for _, _, _, v in ran] == [_code(form)]
+    assert [v for _, _, _, v in ran] == [code]
     a = x.permute(0, 3, 1, 2)
     if up:
         a = a.repeat_interleave(2, 2).repeat_interleave(2, 3)
@@ -143,6 +128,30 @@ def test_conv_each_form(form, B, H, W, C1, C2, Co, stride, up):
         mag = (wf.abs() @ cols.abs()).T + b.double().abs()
         _check(got[i].reshape(ho * wo, Co).double().cpu().numpy(), ref.cpu().numpy(),
                mag.cpu().numpy(), 9 * C)
+
+
+@pytest.mark.parametrize("form,M,N,K", [
+    (0, 20552, 648, 192), (1, 21797, 264, 5120), (2, 16652, 264, 192), (3, 16548, 136, 320),
+    (4, 16412, 88, 64), (5, 16396, 8, 64), (6, 8283, 72, 192), (7, 517, 4360, 192), (8, 1, 8, 64)])
+def test_linear_each_form(form, M, N, K):
+    print(f"wide linear form {form} M={M} N={N} K={K}", flush=True)
+    _linear(_code(form), M, N, K)
+
+
+@pytest.mark.parametrize("form,B,H,W,C1,C2,Co,stride,up", [
+    (0, 4, 53, 58, 64, 0, 168, 1, 1), (0, 8, 43, 72, 64, 64, 416, 1, 0),
+    (0, 8, 66, 68, 64, 0, 1640, 2, 0), (1, 3, 61, 70, 320, 128, 264, 1, 1),
+    (1, 8, 62, 68, 320, 128, 1944, 2, 0), (2, 6, 45, 31, 64, 64, 144, 1, 1),
+    (2, 8, 52, 58, 64, 0, 1288, 2, 0), (3, 8, 67, 31, 64, 64, 136, 1, 0),
+    (3, 8, 56, 60, 64, 0, 536, 2, 0), (4, 4, 46, 34, 64, 64, 168, 1, 1),
+    (4, 8, 60, 52, 64, 0, 904, 2, 0), (5, 4, 57, 72, 64, 64, 8, 1, 0),
+    (5, 8, 70, 66, 64, 0, 136, 2, 0), (5, 3, 36, 38, 64, 0, 8, 1, 1),
+    (6, 4, 35, 15, 64, 64, 88, 1, 1), (6, 8, 72, 70, 64, 0, 72, 2, 0),
+    (7, 1, 50, 42, 64, 64, 72, 1, 1), (7, 8, 70, 60, 128, 0, 72, 2, 0),
+    (8, 1, 4, 4, 64, 64, 8, 2, 0)])
+def test_conv_each_form(form, B, H, W, C1, C2, Co, stride, up):
+    print(f"wide conv form {form} {B}x{H}x{W} {C1}+{C2}->{Co} s{stride} u{up}", flush=True)
+    _conv(_code(form), B, H, W, C1, C2, Co, stride, up)
 
 
 # forms of the self-attention's q | k | v (folded LayerNorm, V transposed), of the cross-attention's
@@ -181,3 +190,26 @@ def test_network_epilogues(C, heads, B, qkv, q, ff1):
                 assert np.abs(got[b].cpu().numpy() - ora(x[b], ts, ctx[b])).max() <= 1e-2
     finally:
         net.close()
+
+
+# tile rows, tile columns and splits of K; four and eight waves share a code (64 x 64 takes four
+# beyond 512 workgroups, 128 x 128 for a long K over at least 128 tiles)
+@pytest.mark.parametrize("bm,bn,splits,M,N,K", [
+    (128, 128, 1, 8200, 964, 192), (128, 128, 1, 13200, 300, 128), (128, 128, 1, 8200, 965, 192),
+    (64, 128, 1, 8200, 700, 192), (64, 128, 1, 1600, 1924, 128), (64, 64, 1, 2200, 1092, 192),
+    (64, 64, 1, 1300, 668, 320), (64, 64, 1, 1300, 701, 320), (64, 64, 4, 300, 668, 2560),
+    (64, 64, 2, 1200, 1004, 4096), (128, 128, 3, 1500, 1708, 8192)])
+def test_linear_small_tiles(bm, bn, splits, M, N, K):
+    print(f"small-tile linear {bm}x{bn}/{splits} M={M} N={N} K={K}", flush=True)
+    _linear(bm * 10_000 + bn * 10 + splits, M, N, K)
+
+
+@pytest.mark.parametrize("bm,bn,splits,B,H,W,C1,C2,Co,stride,up", [
+    (128, 128, 1, 4, 128, 128, 64, 0, 36, 1, 0), (64, 128, 1, 3, 64, 60, 64, 0, 332, 1, 0),
+    (64, 64, 1, 5, 60, 60, 64, 0, 68, 1, 0), (64, 64, 1, 3, 20, 20, 64, 64, 37, 1, 0),
+    (64, 64, 1, 2, 20, 22, 64, 0, 260, 2, 0), (64, 64, 9, 2, 9, 10, 320, 320, 100, 1, 1),
+    (128, 128, 9, 2, 30, 34, 640, 0, 260, 1, 0), (128, 128, 3, 2, 46, 45, 640, 384, 516, 1, 0)])
+def test_conv_small_tiles(bm, bn, splits, B, H, W, C1, C2, Co, stride, up):
+    print(f"small-tile conv {bm}x{bn}/{splits} {B}x{H}x{W} {C1}+{C2}->{Co} s{stride} u{up}",
+          flush=True)
+    _conv(bm * 10_000 + bn * 10 + splits, B, H, W, C1, C2, Co, stride, up)
