@@ -421,6 +421,81 @@ __global__ void __launch_bounds__(256) top_lists_k(const double* __restrict__ cs
   }
 }
 
+// Canonical score of one row by one thread, straight from global memory, 64 values
+// requested ahead of those being added.
+__device__ inline double canon_thread(const double* qd, const char* __restrict__ rows, int r,
+                                      int bf, int d) {
+  double s = 0.0;
+  const int nch = d >> 3;  // chunks of 8 values
+  auto add8 = [&](int c, const float(&x)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = __dadd_rn(s, qd[c * 8 + e] * (double)x[e]);
+  };
+  if (bf) {
+    const u32x4* p = (const u32x4*)((const uint16_t*)rows + (int64_t)r * d);
+    u32x4 v[2][8];
+    auto fetch = [&](int c0, u32x4(&w)[8]) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (c0 + u < nch) w[u] = p[c0 + u];
+    };
+    auto sum = [&](int c0, const u32x4(&w)[8]) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (c0 + u >= nch) break;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t a = w[u][e];
+          x[2 * e] = __uint_as_float(a << 16);
+          x[2 * e + 1] = __uint_as_float(a & 0xFFFF0000u);
+        }
+        add8(c0 + u, x);
+      }
+    };
+    fetch(0, v[0]);
+    for (int c0 = 0; c0 < nch; c0 += 16) {
+      fetch(c0 + 8, v[1]);
+      sum(c0, v[0]);
+      fetch(c0 + 16, v[0]);
+      sum(c0 + 8, v[1]);
+    }
+  } else {
+    const u32x4* p = (const u32x4*)((const float*)rows + (int64_t)r * d);
+    u32x4 v[2][8];  // 4 chunks of 8 values each
+    auto fetch = [&](int c0, u32x4(&w)[8]) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c0 + u < nch) {
+          w[2 * u] = p[2 * (c0 + u)];
+          w[2 * u + 1] = p[2 * (c0 + u) + 1];
+        }
+    };
+    auto sum = [&](int c0, const u32x4(&w)[8]) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (c0 + u >= nch) break;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t a = w[2 * u][e], b = w[2 * u + 1][e];
+          x[e] = __uint_as_float(a);
+          x[4 + e] = __uint_as_float(b);
+        }
+        add8(c0 + u, x);
+      }
+    };
+    fetch(0, v[0]);
+    for (int c0 = 0; c0 < nch; c0 += 8) {
+      fetch(c0 + 4, v[1]);
+      sum(c0, v[0]);
+      fetch(c0 + 8, v[0]);
+      sum(c0 + 4, v[1]);
+    }
+  }
+  return s;
+}
+
 // Best probed row per (query, probe, chunk of 256 list positions).  Groups of 8
 // lanes take float64 dots of the rows in another summation order, each within
 // tol = 2^-40 |q| |c| of the canonical score (2 d 2^-53 |q| |c| at most, d <=
@@ -435,6 +510,13 @@ __global__ void __launch_bounds__(256) top_lists_k(const double* __restrict__ cs
 // such a block is summed and the scores are compared in the fixed tree of
 // probe_final_k over list positions.
 constexpr int PS_T = 512;
+// Rows to sum beyond which every row gets a thread of its own: a wave's sum of a row
+// costs about as much as a thread's of all rows of its wave, and four waves share the
+// rows, so past two rows a wave the threads win (200000 x 768 bf16, one query equal
+// to that many rows, 16 of 256 lists, waves against threads: 16 rows 67 and 68 us, 64
+// rows 84 and 69, 120 rows 89 and 69, 300 rows 377 and 71, 20000 rows 1495 and 164;
+// no equal rows 63; f32, 384 wide, 300 rows 174 and 53).
+constexpr int PS_FEW = 8;
 
 __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q, int d,
                                                      const void* __restrict__ lrows, int bf,
@@ -552,7 +634,26 @@ __global__ void __launch_bounds__(PS_T) probe_scan_k(const float* __restrict__ q
   double bs = -INFINITY;
   int64_t bi = -1;
   const int ns = n_surv;
-  if (wave < NWV / 2) {
+  if (ns > PS_FEW) {
+    if (t < ns) {
+      const int r = surv[t];
+      const double s = canon_thread(qd, rows, r, bf, d);
+      if (any_nan) {
+        fast[r] = s;
+      } else {
+        bs = s;
+        bi = ids[r];
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double s2 = __shfl_xor(bs, o, 64);
+      const int64_t i2 = __shfl_xor(bi, o, 64);
+      if (i2 >= 0 && (bi < 0 || better_pair(s2, i2, bs, bi))) {
+        bs = s2;
+        bi = i2;
+      }
+    }
+  } else if (wave < NWV / 2) {
     double* prod = prods + (size_t)wave * q_padded(d);
     for (int i = wave; i < ns; i += NWV / 2) {
       const int r = surv[i];

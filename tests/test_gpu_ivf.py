@@ -101,6 +101,28 @@ def _tree(scores, ids):
     return s[0], i[0]
 
 
+# one list of one block: rows to sum on both sides of the line between a wave and a thread a row
+@pytest.mark.parametrize("dtype,d", [("bf16", 136), ("f32", 72), ("bf16", 2048)])
+@pytest.mark.parametrize("same", [8, 9, 64, 65, 256])
+def test_equal_rows_of_one_block(dtype, d, same):
+    import paper_2312_04429_amd as P
+    n = 256
+    print(f"ivf equal rows d={d} {dtype} same={same}", flush=True)
+    X = synth.make_cache(n, d, 12, 0.15, d, dtype)
+    at = np.sort(np.random.default_rng(same).choice(n, same, replace=False))
+    X[at] = X[at[0]]
+    init = np.array([0])
+    index = P.NvIVF(_dev(X), init, 0)
+    rows = synth.from_bf16_bits(X) if dtype == "bf16" else X
+    q = np.stack([rows[at[0]] / np.linalg.norm(rows[at[0]]), -rows[at[0]]]).astype(np.float32)
+    c, lists, perm, off = ivf.build(X, init, 0)
+    gi, gs, gk = index.search(torch.from_numpy(q).cuda(), 1, T, K)
+    oi, os_, ok, _ = ivf.search(q, X, c, perm, off, 1, T, K)
+    assert gi.cpu().numpy().tolist() == oi.tolist() and gi[0].item() == at[0]
+    assert np.array_equal(gs.cpu().numpy(), os_)
+    assert gk.cpu().numpy().tolist() == ok.tolist()
+
+
 @pytest.mark.parametrize("n,d,dtype,L", [(900, 64, "f32", 2), (700, 72, "bf16", 3)])
 def test_rows_that_are_not_finite(n, d, dtype, L):
     """Scores that are not numbers are ordered by the comparison tree alone: with NaN and infinite
