@@ -154,10 +154,10 @@ inline float split_cost(const StreamPlan& p, const StreamShape& g) {
 // if it is up to 6 % above (the estimates are good to about 10 % each, and the
 // timings above had the fewest wrong choices there).  Unsplit gemm_s is not
 // priced: the wide forms are its equals or better wherever both apply, but for
-// GEGLU, whose two forms leave most CUs without a tile up to 320 tiles of 128 x 128
-// (inside the network 128 x 10240 x 1280 19.0 us on small tiles, 26.3 on form 4;
-// 512 x 5120 x 640 14.1 and 14.9; 512 x 10240 x 1280, 320 tiles, 31.6 and 31.8; 768
-// x 10240 x 1280, 480 tiles, 44.0 and 31.7).
+// GEGLU, whose two forms have few tiles and are slower up to 320 of 128 x 128 (inside
+// the network 128 x 10240 x 1280, 80 tiles, 19.0 us on small tiles, 26.3 on form 4;
+// 512 x 5120 x 640, 160 tiles, 14.1 and 14.9; 512 x 10240 x 1280, 320 tiles, 31.6 and
+// 31.8; 768 x 10240 x 1280, 480 tiles, 44.0 and 31.7).
 inline StreamPlan stream_plan(const StreamShape& g) {
   const StreamPlan s = gemm_s_plan(g);
   if (!g.rows_ok || (g.geglu && tiles_of(g, 128, 128) <= 320)) return s;
